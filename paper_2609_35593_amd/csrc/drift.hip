@@ -4,15 +4,30 @@
 // x_t^T M_h x_t = ||W_O^h x_t||^2, with x_t = a_t - b_t the difference of two
 // float32 attention outputs of the same queries.
 //
-// One workgroup per (head, query block), 4 waves; a wave takes every fourth
-// token of the block, lane <-> channel: x in float64 (the difference of two
-// float32 values is exact there), M_h x by broadcasts of x from the wave's LDS
-// area against M_h's rows in LDS, x . (M_h x) by a wave butterfly, summed over
-// the wave's tokens in order and then over the 4 waves in order.
+// One workgroup of 4 waves per (head, query block); wave w takes the block's
+// 16-token tiles w, w + 4. A tile is a float64 matrix product on the matrix cores
+// (16x16x4 steps), U^T = M X^T, with everything a lane needs already in its
+// registers:
+//  - lane l holds channels 16 u + 4 g + e (u, e = 0..3, g = l / 16) of token l % 16
+//    as 16 float64 values (the difference of two float32 values is exact): four
+//    16-byte loads per input, each covering 64 contiguous bytes of 16 tokens. They
+//    are the B operands of the steps (u, e) as they lie;
+//  - row r of the product's 16-row block nt stands for channel 16 nt + 4 (r % 4) +
+//    r / 4, so result register v of lane l (row 4 v + g) is channel 16 nt + 4 g + v,
+//    the x value the lane holds as (u = nt, e = v): x . (M x) needs no exchange;
+//  - the quadratic form folds M's off-diagonal 16 x 16 blocks (nt, u) and (u, nt)
+//    into one (M + M^T, exact or once rounded in float64), so 10 of the 16 blocks
+//    are multiplied. Their A operands, 40 float64 values a lane, are read once per
+//    wave and stay in registers.
+// Roofline: 1.25 GFLOP of float64 matrix steps and 90 MB (two float32 inputs) at 16
+// heads x 10,992 tokens, 14 and 18 us at 78.6 TFLOP/s and 5.1 TB/s. Measured there:
+// 30 us (one lane per channel with M and x read from LDS for every token: 145 us).
 #include "ress_internal.h"
 
 namespace ress {
 namespace {
+
+typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
@@ -24,33 +39,75 @@ __device__ __forceinline__ double wave_sum(double x)
     return x;
 }
 
-__global__ void __launch_bounds__(kThreads) drift_sq_kernel(const DriftSqParams p)
+__global__ void __launch_bounds__(kThreads, 2) drift_sq_kernel(const DriftSqParams p)
 {
-    __shared__ float Ms[kD * (kD + 1)];
-    __shared__ __align__(16) double xs[kWaves][kD];
     __shared__ double part[kWaves];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = blockIdx.x / p.n_qb, i = blockIdx.x % p.n_qb;
-    const float *Mh = p.gram + (size_t)h * kD * kD;
-    for (int e = tid; e < kD * kD; e += kThreads) Ms[(e >> 6) * (kD + 1) + (e & 63)] = Mh[e];
-    __syncthreads();
     const int t0 = i * p.bq, t1 = min(t0 + p.bq, p.N);
-    double acc = 0.0;
-    for (int t = t0 + wave; t < t1; t += kWaves) {
-        const size_t off = ((size_t)h * p.N + t) * kD + lane;
-        const double x = (double)p.a[off] - (double)p.b[off];
-        xs[wave][lane] = x;
-        __builtin_amdgcn_wave_barrier();
-        double u = 0.0;
-#pragma unroll 8
-        for (int c = 0; c < kD; c += 2) {
-            const double2 xc = *reinterpret_cast<const double2 *>(&xs[wave][c]);
-            u = fma((double)Ms[lane * (kD + 1) + c + 1], xc.y, fma((double)Ms[lane * (kD + 1) + c], xc.x, u));
+    const int g = lane >> 4, col = lane & 15;
+    const float *Mh = p.gram + (size_t)h * kD * kD;
+
+    // The two inputs' 16 channels of this lane's token (rows past the block repeat its
+    // last row; their x is zeroed).
+    auto load = [&](int t, float4 (&xa)[4], float4 (&xb)[4]) __attribute__((always_inline)) {
+        const size_t off = ((size_t)h * p.N + min(t + col, t1 - 1)) * kD + 4 * g;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            xa[u] = *reinterpret_cast<const float4 *>(p.a + off + 16 * u);
+            xb[u] = *reinterpret_cast<const float4 *>(p.b + off + 16 * u);
         }
-        acc += wave_sum(x * u);
-        __builtin_amdgcn_wave_barrier();
+    };
+    float4 xa[4], xb[4];
+    int t = t0 + 16 * wave;
+    if (t < t1) load(t, xa, xb);
+
+    double m[4][4][4];  // A operand of block (nt, u >= nt), step e
+    if (t < t1) {
+        const int chan = 4 * (col & 3) + (col >> 2);  // channel of row `col` within its block
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+            for (int u = nt; u < 4; ++u) {
+                const int row = 16 * nt + chan, c0 = 16 * u + 4 * g;
+                const float4 v = *reinterpret_cast<const float4 *>(Mh + row * kD + c0);
+                const float w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    m[nt][u][e] = u == nt ? (double)w[e] : (double)w[e] + (double)Mh[(c0 + e) * kD + row];
+            }
     }
+
+    double acc = 0.0;
+    for (; t < t1; t += 16 * kWaves) {
+        double x[4][4];
+        const bool in = t + col < t1;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            x[u][0] = in ? (double)xa[u].x - (double)xb[u].x : 0.0;
+            x[u][1] = in ? (double)xa[u].y - (double)xb[u].y : 0.0;
+            x[u][2] = in ? (double)xa[u].z - (double)xb[u].z : 0.0;
+            x[u][3] = in ? (double)xa[u].w - (double)xb[u].w : 0.0;
+        }
+        if (t + 16 * kWaves < t1) load(t + 16 * kWaves, xa, xb);
+        v4d c[4];
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) c[nt] = v4d{0.0, 0.0, 0.0, 0.0};
+        // Independent chains of the four row blocks side by side.
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int nt = 0; nt <= u; ++nt)
+                    c[nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(m[nt][u][e], x[u][e], c[nt], 0, 0, 0);
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc = fma(x[nt][v], c[nt][v], acc);
+    }
+    acc = wave_sum(acc);
     if (lane == 0) part[wave] = acc;
     __syncthreads();
     if (tid == 0) {

@@ -5,23 +5,32 @@
 // Work layout. A workgroup of NW waves owns NW x R query blocks ("rows") of one
 // head; each wave owns R of them.
 //  - Per-candidate quantities live "lane <-> key block": lane l, slot c holds key
-//    block j = l + 64 c (CPL slots). Per-row vectors (Qbar, vbar, S vbar with S
-//    the symmetric part of M, g, M g) live in the wave's LDS area, channel d at
-//    index d.
+//    block j = l + 64 c (CPL slots). P_ij and s_ij^2 stay in registers for all rounds;
+//    product results, order keys and swap lists take turns in one LDS staging row per
+//    row. The vectors that a product needs from every row (Qbar, vbar, S vbar with S
+//    the symmetric part of M, g, M g) pass through two LDS vector slots per row; the
+//    owner keeps vbar and g lane <-> channel in registers.
 //  - The contractions are float64 matrix products of the workgroup's rows
 //    (padded to a multiple of 16) with the head's row-major pooled tensors, on
 //    the matrix cores (16x16x4 float64 steps): over channels, the pooled logits
 //    against Kbar and the drift scores (expanded as in Eq. 9; a row's block with
 //    P > 1/2 gets e^T M e directly) and every round's gains against Vbar;
 //    over key blocks, the dense pooled output vbar and the net drift g against
-//    Vbar. The pooled tensor goes from L2 straight into the B operands (each lane
-//    reads 16 contiguous bytes or more of one key block); the A operands are the
-//    rows' LDS vectors, or their weights staged in LDS; result tiles pass through
-//    the LDS staging area into the layout of the owning wave. Each output element
-//    is one chain of matrix steps in a fixed order: reruns are bit-identical.
-//  - Every top-k is exact: a bitwise search for the k-th largest of
-//    order-preserving 64-bit keys, using wave ballots and popcounts, ties broken
-//    by the lower block index. No atomics and no data-dependent reduction order.
+//    Vbar. Each output element is one chain of matrix steps in a fixed order: reruns
+//    are bit-identical.
+//  - Every top-k is exact: a search for a threshold of order-preserving 64-bit keys
+//    that exactly k reach, using wave ballots and popcounts, ties broken by the lower
+//    block index. No atomics and no data-dependent reduction order.
+//
+// What bounds it. Row work (gains, searches, swap lists) is a chain of short vector
+// and scalar steps, so it wants waves: up to 16 per workgroup, one workgroup per CU,
+// which is why a row's results wait in LDS and not in registers (128 to 256 per lane).
+// The products want 16 rows per tile and their B tiles in few cache-line requests
+// (load_tile). Measured (select_kernel alone, 16 heads, us; before: 8 waves of one to
+// three rows with the products' results in registers): 8 views 46 -> 42, 16 views
+// 88 -> 63, 32 views 192 -> 160, 100 views 2,010 -> 1,160; with 64-token key blocks 16
+// views 130 -> 92, 32 views 475 -> 282 and (4 heads) 100 views 4,520 -> 1,140. Of the
+// 100-view time the products take about 45%, the searches 15%, gains 10-15%.
 // All arithmetic is float64 (the discrete decisions stay stable).
 #include <math.h>
 
@@ -123,41 +132,6 @@ __device__ __forceinline__ void wave_sum2(double a, double b, double &sa, double
     sb = swap_sum<true>(b);
 }
 
-template <int CTRL>
-__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long u)
-{
-    const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)u, CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), CTRL, 0xf, 0xf, false);
-    return ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;
-}
-
-template <bool ROW32>
-__device__ __forceinline__ unsigned long long swap_max_u64(unsigned long long u)
-{
-    const unsigned lo = (unsigned)u, hi = (unsigned)(u >> 32);
-    const auto a = ROW32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
-                         : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-    const auto b = ROW32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
-                         : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    const unsigned long long d0 = ((unsigned long long)b[0] << 32) | a[0];
-    const unsigned long long d1 = ((unsigned long long)b[1] << 32) | a[1];
-    return d0 > d1 ? d0 : d1;
-}
-
-// Largest 64-bit unsigned value over the wave, in every lane.
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long x)
-{
-    unsigned long long y = dpp_u64<0xB1>(x);
-    x = y > x ? y : x;
-    y = dpp_u64<0x4E>(x);
-    x = y > x ? y : x;
-    y = dpp_u64<0x141>(x);
-    x = y > x ? y : x;
-    y = dpp_u64<0x140>(x);
-    x = y > x ? y : x;
-    return swap_max_u64<true>(swap_max_u64<false>(x));
-}
-
 __device__ __forceinline__ double wave_max(double x)
 {
     x = fmax(x, dpp_f64<0xB1>(x));
@@ -184,251 +158,202 @@ __device__ __forceinline__ unsigned long long order_key(double x)
     return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
 }
 
-// Bitwise search over member high words h[0..NS) (zero for non-members): the
-// largest t such that at least k of them reach t with a zero low word below it,
-// built bit by bit; found = exactly k reach it. The threshold, bit and counts are
-// wave-uniform and the loop has a single exit, so that it runs on scalar
-// registers and scalar branches.
+// One bit per slot of a lane.
+template <bool WIDE>
+struct slot_bits {
+    using type = unsigned int;
+};
+template <>
+struct slot_bits<true> {
+    using type = unsigned long long;
+};
+
+// x / d for normal d far from the ends of the range and finite x: the reciprocal
+// by two Newton steps and one corrected quotient, without the compiler's scaling
+// and special cases (a third fewer instructions; the same value but for a last bit
+// now and then).
+__device__ __forceinline__ double quot(double x, double d)
+{
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    r = fma(fma(-d, r, 1.0), r, r);
+    const double q = x * r;
+    return fma(fma(-d, q, x), r, q);
+}
+
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ double uniform(double x)
+{
+    const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)u);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(u >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+template <int CTRL>
+__device__ __forceinline__ unsigned int dpp_max_u32(unsigned int x)
+{
+    const unsigned int y = (unsigned int)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xf, 0xf, false);
+    return y > x ? y : x;
+}
+
+// Largest 32-bit unsigned value over the wave, as a scalar.
+__device__ __forceinline__ unsigned int wave_max_u32(unsigned int x)
+{
+    x = dpp_max_u32<0xB1>(x);
+    x = dpp_max_u32<0x4E>(x);
+    x = dpp_max_u32<0x141>(x);
+    x = dpp_max_u32<0x140>(x);
+    auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = a[0] > a[1] ? a[0] : a[1];
+    a = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return __builtin_amdgcn_readfirstlane(a[0] > a[1] ? a[0] : a[1]);
+}
+
+// Threshold search over member high words h[0..NS) (zero for non-members): a t that
+// exactly k of them reach (found), or else the k-th largest word, which more than k
+// reach. From the largest word down in steps of 1/4 octave (of the float64 value
+// behind the word), 1, 4, 16, ... octaves, then by halving: the k-th largest of a few
+// hundred gains mostly lies within two octaves of the largest, and 4-6 counts find a
+// separating threshold (measured over the 8- and 32-view layers; bit by bit from the
+// top: 14-18). lo is reached by at least k members, hi by fewer (0 < hi - lo in
+// modular arithmetic, it shrinks with every count). All of it wave-uniform, on scalar
+// registers and branches.
 template <int NS>
 __device__ __forceinline__ unsigned int search_high(const unsigned int (&h)[NS], int k, int &found)
 {
-    unsigned int thi = 0, bit = 0x80000000u;
-    do {
-        const unsigned int cand = __builtin_amdgcn_readfirstlane(thi | bit);
-        unsigned long long bl[NS];
+    unsigned int m = h[0];
 #pragma unroll
-        for (int c = 0; c < NS; ++c) bl[c] = __ballot(h[c] >= cand);
+    for (int c = 1; c < NS; ++c) m = h[c] > m ? h[c] : m;
+    unsigned int t = wave_max_u32(m), at, lo = 0, hi = t + 1, step = 1u << 18;
+    do {
         int cnt = 0;
 #pragma unroll
-        for (int c = 0; c < NS; ++c) cnt += __popcll(bl[c]);
-        thi = cnt >= k ? cand : thi;
+        for (int c = 0; c < NS; ++c) cnt += __popcll(__ballot(h[c] >= t));
         found = cnt == k;
-        bit >>= 1;
-    } while (!found && bit != 0u);
-    return thi;
+        at = t;
+        lo = cnt > k ? t : lo;
+        hi = cnt > k ? hi : t;
+        const unsigned int down = hi > step ? hi - step : 1u, mid = lo + ((hi - lo) >> 1);
+        t = __builtin_amdgcn_readfirstlane(lo == 0u ? down : mid);
+        step = step >= 1u << 30 ? ~0u : step << 2;
+    } while (!found && hi - lo != 1u);
+    return found ? at : lo;
 }
 
-// The member high words packed into the first NS slots (zero past them) through
-// the wave's scratch scr (this wave's LDS only), when at most 64 NS are members.
-template <int CPL, int NS>
-__device__ __forceinline__ void pack_high(const unsigned int (&hi)[CPL], unsigned long long mbits, int nmem,
-                                          unsigned int *scr, unsigned long long lane_lt, int lane,
-                                          unsigned int (&h)[NS])
-{
-    int base = 0;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-        const bool m = (mbits >> c) & 1ull;
-        const unsigned long long bl = __ballot(m);
-        if (m) scr[base + __popcll(bl & lane_lt)] = hi[c];
-        base += __popcll(bl);
-    }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int c = 0; c < NS; ++c) h[c] = 64 * c + lane < nmem ? scr[64 * c + lane] : 0u;
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Exact top-k of the member slots by (key desc, block index asc). Bit c of
-// mbits marks this lane's slot c as a member. Non-member keys are replaced by 0,
-// below every member key (an order key of a finite value is at least 1), so one
-// ballot per slot counts members only. The k-th largest key is found bit by
-// bit, high word first (search_high); when the members fit 2 or 4 slots and a
-// scratch is given, that search runs on them packed (same threshold, fewer
-// compares). Once the high word t of the k-th largest key is known, a key
-// reaches a candidate (t, x) (x >= 1) exactly when the 32-bit value "all ones if
-// its high word is above t, its low word if equal, zero if below" reaches x. The
-// search stops as soon as exactly k keys reach the threshold. Returns this
-// lane's chosen slots as a bit mask. Requires 0 <= k <= number of members.
+// Exact top-k of the member slots by (key desc, block index asc). The slots' order
+// keys are the 8-byte words keys[64 c] (this lane's pointer into its wave's LDS row;
+// they are read from there for each search, which needs one register a slot). Bit c of mbits marks
+// this lane's slot c as a member. Non-member high words are replaced by 0, below
+// every member's (an order key of a finite value has a nonzero high word), so one
+// ballot per slot counts members only. search_high first; where no high word
+// separates the top k, a key reaches a candidate (t, x) (x >= 1), t the k-th largest
+// high word, exactly when the 32-bit value "all ones if its high word is above t, its
+// low word if equal, zero if below" reaches x, and the low word is found bit by bit.
+// Returns this lane's chosen slots as a bit mask. Requires 0 <= k <= number of
+// members.
 template <int CPL>
-__device__ __forceinline__ unsigned long long topk_slots(const unsigned long long (&key)[CPL],
-                                                         unsigned long long mbits, int k, unsigned long long lane_lt,
-                                                         unsigned int *scr = nullptr, int lane = 0)
+__device__ __forceinline__ typename slot_bits<(CPL > 32)>::type topk_slots(const double *keys,
+                                                                           typename slot_bits<(CPL > 32)>::type mbits,
+                                                                           int k, unsigned long long lane_lt)
 {
     k = __builtin_amdgcn_readfirstlane(k);
-    if (k <= 0) return 0ull;
-    unsigned int hi[CPL], lo[CPL];
+    if (k <= 0) return 0;
+    unsigned int hm[CPL];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-        const unsigned long long km = ((mbits >> c) & 1ull) ? key[c] : 0ull;
-        hi[c] = (unsigned int)(km >> 32);
-        lo[c] = (unsigned int)km;
-    }
+    for (int c = 0; c < CPL; ++c)
+        hm[c] = ((mbits >> c) & 1) ? (unsigned int)((unsigned long long)__double_as_longlong(keys[64 * c]) >> 32) : 0u;
     int found = 0;
-    unsigned int thi;
-    int nmem = 64 * CPL;
-    if (scr != nullptr && CPL > 2) {
-        nmem = 0;
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) nmem += __popcll(__ballot((mbits >> c) & 1ull));
-    }
-    if (CPL > 2 && nmem <= 128) {
-        unsigned int h[2];
-        pack_high<CPL, 2>(hi, mbits, nmem, scr, lane_lt, lane, h);
-        thi = search_high<2>(h, k, found);
-    } else if (CPL > 4 && nmem <= 256) {
-        unsigned int h[4];
-        pack_high<CPL, 4>(hi, mbits, nmem, scr, lane_lt, lane, h);
-        thi = search_high<4>(h, k, found);
-    } else {
-        thi = search_high<CPL>(hi, k, found);
-    }
+    const unsigned int thi = search_high<CPL>(hm, k, found);
+    typename slot_bits<(CPL > 32)>::type chosen = 0;
+    const auto one = (typename slot_bits<(CPL > 32)>::type)1;
     if (found) {  // exactly k keys reach (thi, 0): they are the top k
-        unsigned long long chosen = 0;
 #pragma unroll
         for (int c = 0; c < CPL; ++c)
-            if (hi[c] >= thi) chosen |= 1ull << c;
-        return chosen;
+            if (hm[c] >= thi) chosen |= one << c;
+        return chosen & mbits;
     }
     // Low word, against the high word thi of the k-th largest key.
     unsigned int l2[CPL];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) l2[c] = hi[c] > thi ? 0xffffffffu : (hi[c] == thi ? lo[c] : 0u);
+    for (int c = 0; c < CPL; ++c)
+        l2[c] = hm[c] > thi ? 0xffffffffu
+                            : (hm[c] == thi ? (unsigned int)__double_as_longlong(keys[64 * c]) : 0u);
     unsigned int tlo = 0, bit = 0x80000000u;
     do {
         const unsigned int cand = __builtin_amdgcn_readfirstlane(tlo | bit);
-        unsigned long long bl[CPL];
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) bl[c] = __ballot(l2[c] >= cand);
         int cnt = 0;
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) cnt += __popcll(bl[c]);
+        for (int c = 0; c < CPL; ++c) cnt += __popcll(__ballot(l2[c] >= cand));
         tlo = cnt >= k ? cand : tlo;
         found = cnt == k;
         bit >>= 1;
     } while (!found && bit != 0u);
     if (found) {
-        unsigned long long chosen = 0;
 #pragma unroll
         for (int c = 0; c < CPL; ++c)
-            if (l2[c] >= tlo) chosen |= 1ull << c;
-        return chosen;
+            if (l2[c] >= tlo) chosen |= one << c;
+        return chosen & mbits;
     }
-    // thr is the k-th largest key and is tied: take all larger keys and the
+    // (thi, tlo) is the k-th largest key and is tied: take all larger keys and the
     // lowest-index ties.
-    const unsigned long long thr = ((unsigned long long)thi << 32) | tlo;
-    unsigned long long km[CPL];
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) km[c] = ((unsigned long long)hi[c] << 32) | lo[c];
     int gt = 0;
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) gt += __popcll(__ballot(km[c] > thr));
+    for (int c = 0; c < CPL; ++c) gt += __popcll(__ballot(hm[c] > thi || (hm[c] == thi && l2[c] > tlo)));
     const int need = k - gt;
     int before = 0;
-    unsigned long long chosen = 0;
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
-        const bool tie = km[c] == thr;
+        const bool above = hm[c] > thi || (hm[c] == thi && l2[c] > tlo);
+        const bool tie = hm[c] == thi && l2[c] == tlo;
         const unsigned long long tb = __ballot(tie);
         const int rank = before + __popcll(tb & lane_lt);
-        if (km[c] > thr || (tie && rank < need)) chosen |= 1ull << c;
+        if (above || (tie && rank < need)) chosen |= one << c;
         before += __popcll(tb);
     }
-    return chosen;
+    return chosen & mbits;
 }
 
-// The same selection as topk_slots for small k, by k extractions of the largest
-// remaining member key: per lane the largest over its slots (lowest slot on
-// ties), then over the wave (wave_max_u64), then the lowest block index among
-// the slots holding that key (slots in ascending order, lanes in ascending
-// order within a slot, which is ascending block index).
-template <int CPL>
-__device__ __forceinline__ unsigned long long topk_small(const unsigned long long (&key)[CPL],
-                                                         unsigned long long mbits, int k, int lane)
-{
-    unsigned long long left = mbits, chosen = 0;
-    for (int t = 0; t < k; ++t) {
-        unsigned long long best = 0;
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) {
-            const unsigned long long v = ((left >> c) & 1ull) ? key[c] : 0ull;
-            best = v > best ? v : best;
-        }
-        best = wave_max_u64(best);
-        // best > 0: at least one member is left (k <= members)
-        bool done = false;
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) {
-            const unsigned long long at = __ballot(((left >> c) & 1ull) && key[c] == best);
-            if (!done && at != 0ull) {
-                if (lane == __builtin_ctzll(at)) {
-                    left &= ~(1ull << c);
-                    chosen |= 1ull << c;
-                }
-                done = true;
-            }
-        }
-    }
-    return chosen;
-}
-
-// Top-k of the member slots: extraction for k up to 2, bitwise search beyond
-// (measured: extraction costs more than the search from k = 5 on); scr as for
-// topk_slots.
-template <int CPL>
-__device__ __forceinline__ unsigned long long topk_any(const unsigned long long (&key)[CPL],
-                                                       unsigned long long mbits, int k, int lane,
-                                                       unsigned long long lane_lt, unsigned int *scr)
-{
-    return k <= 2 ? topk_small<CPL>(key, mbits, k, lane) : topk_slots<CPL>(key, mbits, k, lane_lt, scr, lane);
-}
-
-// Swap count of round r (Eq. 17): max(floor, floor(rho c 2^-(r+1))).
-__device__ __forceinline__ int swaps_of_round(int c, double rho, int r, int swap_floor)
-{
-    const int m = (int)floor(rho * (double)c * ldexp(1.0, -(r + 1)));
-    return m > swap_floor ? m : swap_floor;
-}
-
-// Per-wave LDS area (doubles): vectors vec[slot][R][64] and a swap list of up to
-// 64 (block, weight) pairs plus padding to a multiple of 8. Every part starts on
-// a 16-byte boundary.
-template <int R>
-struct WaveLds {
-    static constexpr int kVecs = 3;  // 0: Qbar then vbar, 1: S vbar then M g, 2: g
-    static constexpr int kSwaps = 72;
-    static constexpr int kDoubles = kVecs * R * kD + kSwaps + kSwaps / 2;
-    static_assert(kDoubles % 2 == 0, "16-byte aligned wave areas");
-    double *base;
-    __device__ double *vec(int slot, int r) const { return base + (slot * R + r) * kD; }
-    __device__ double *swap_w() const { return base + kVecs * R * kD; }
-    __device__ int *swap_j() const { return reinterpret_cast<int *>(base + kVecs * R * kD + kSwaps); }
-};
-
-// Sizes of a workgroup configuration: RW rows in MT 16-row tiles; the LDS
-// staging area holds 16 MT rows of CHK slots (64 key blocks each) plus 2 doubles
-// of padding per row (so that rows start on different 16-byte bank groups), as
-// many slots as the LDS left by the wave areas and M_h allows.
+// Sizes of a workgroup configuration: NW waves of R rows each, RW = NW R rows in MT
+// 16-row tiles. LDS holds, per row, one staging row of SW slots (64 key blocks
+// each, padded by 16 bytes so that rows start on different banks) and two vectors
+// of 64 channels (padded likewise), and M_h where it fits beside them.
 template <int CPL, int R, int NW>
 struct SelCfg {
     static constexpr int RW = NW * R;
     static constexpr int MT = (RW + 15) / 16;
-    static constexpr int WD = WaveLds<R>::kDoubles;
-    static constexpr int FIXED = NW * WD * 8 + kD * (kD + 1) * 4 + 256;
-    static constexpr int chk()
-    {
-        int c = CPL;
-        while (c > 1 && FIXED + 16 * MT * (c * 512 + 16) > 163840) --c;
-        return c;
-    }
-    static constexpr int CHK = chk();
-    static constexpr int SROW = CHK * 64 + 2;          // doubles per staging row
-    static constexpr int NCH = (CPL + CHK - 1) / CHK;  // chunks of slots
     // Key-block splits of the weighted sums: 2 MT KS items, one per wave; the KS
     // partial tiles of a row sit side by side in its staging row.
-    static constexpr int KS = (NW / (2 * MT)) < CHK ? (NW / (2 * MT)) : CHK;
+    static constexpr int KS = NW / (2 * MT) < 8 ? NW / (2 * MT) : 8;
+    static constexpr int SW = CPL > KS ? (CPL > 3 ? CPL : 3) : (KS > 3 ? KS : 3);  // at least 3: the swap list
+    static constexpr int SROW = SW * 64 + 2;  // doubles per staging row
+    static constexpr int VROW = kD + 2;       // doubles per vector
+    static constexpr int BYTES = RW * (SROW + 2 * VROW) * 8;
+    static constexpr bool M_LDS = BYTES + kD * (kD + 1) * 4 + 64 <= 163840;
+    static constexpr int TPW = (4 * CPL + NW - 1) / NW;  // key-block tiles per wave, at most
+    // Tiles of Vbar a wave keeps in registers for all its passes (32 registers
+    // each), as far as they fit beside the rows' state.
+    static constexpr int REGS = 2048 / NW;  // registers per lane: one workgroup per CU
+    static constexpr int STATE = 4 * R * CPL + CPL + 60 + 25 * R;
+    static constexpr int VT = STATE + 32 * TPW <= REGS ? TPW : (STATE + 32 <= REGS ? 1 : 0);
+    static constexpr int FENCE = REGS - 4 * R * CPL - 32 * VT >= 128 ? 0 : (REGS - 4 * R * CPL - 32 * VT >= 90 ? 2 : 1);
+    using bits = typename slot_bits<(CPL > 32)>::type;
+    static_assert(BYTES <= 163840, "LDS of one CU");
     static_assert(KS >= 1, "one weighted-sum item per wave at most");
     static_assert(4 * MT <= NW, "one mat-vec item per wave at most");
 };
 
 template <int CPL, int R, int NW>
-__global__ void __launch_bounds__(NW * 64, 1) select_kernel(const SelectParams p)
+__global__ void __launch_bounds__(NW * 64, NW / 4) select_kernel(const SelectParams p)
 {
     using Cfg = SelCfg<CPL, R, NW>;
-    constexpr int RW = Cfg::RW, MT = Cfg::MT, CHK = Cfg::CHK, SROW = Cfg::SROW, NCH = Cfg::NCH, KS = Cfg::KS;
-    __shared__ __align__(16) double stage[16 * MT * SROW];
-    __shared__ __align__(16) double wareas[NW * Cfg::WD];
-    __shared__ float Ms[kD * (kD + 1)];
+    constexpr int RW = Cfg::RW, MT = Cfg::MT, SROW = Cfg::SROW, VROW = Cfg::VROW, KS = Cfg::KS, VT = Cfg::VT;
+    constexpr int TPW = Cfg::TPW;
+    constexpr bool M_LDS = Cfg::M_LDS;
+    __shared__ __align__(16) double stage[RW * SROW];
+    __shared__ __align__(16) double vecs[2 * RW * VROW];  // vector slots 0 and 1 of every row
+    __shared__ int flags[NW];
+    __shared__ float Ms[M_LDS ? kD * (kD + 1) : 1];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned long long lane_lt = (1ull << lane) - 1ull;
@@ -443,161 +368,202 @@ __global__ void __launch_bounds__(NW * 64, 1) select_kernel(const SelectParams p
     const int ntiles = (nkb + 15) >> 4;
     const __amdgpu_buffer_rsrc_t rsK = pooled_rsrc(p.pooled.kbar + (size_t)h * nkb * kD, nkb);
     const __amdgpu_buffer_rsrc_t rsV = pooled_rsrc(p.pooled.vbar + (size_t)h * nkb * kD, nkb);
-    {
-        const float *Mh = p.gram + (size_t)h * kD * kD;
-        for (int e = tid; e < kD * kD; e += NW * 64) Ms[(e >> 6) * (kD + 1) + (e & 63)] = Mh[e];
-    }
-    // Vector `slot` of the workgroup's row m (in the area of the wave owning it).
-    auto row_vec = [&](int slot, int m) -> double * {
-        return wareas + (m / R) * Cfg::WD + (slot * R + m % R) * kD;
+    const float *Mh = p.gram + (size_t)h * kD * kD;
+    auto m_at = [&](int r, int c) __attribute__((always_inline)) -> double {
+        return (double)(M_LDS ? Ms[r * (kD + 1) + c] : Mh[r * kD + c]);
     };
+    auto row_vec = [&](int slot, int m) __attribute__((always_inline)) -> double * {
+        return vecs + (slot * RW + m) * VROW;
+    };
+    // Keeps the compiler from interleaving the work of more than FENCE slots, whose
+    // temporaries would not fit the registers.
+    auto slot_fence = [&](int c) __attribute__((always_inline)) {
+        if (Cfg::FENCE > 0 && c % (Cfg::FENCE > 0 ? Cfg::FENCE : 1) == Cfg::FENCE - 1) __builtin_amdgcn_sched_barrier(0);
+    };
+    // n_kb anew for each use, so that the compiler compares a slot's block index with it
+    // there instead of keeping one mask per slot.
+    auto nkb_here = [&]() __attribute__((always_inline)) -> int {
+        int n = nkb;
+        asm("" : "+s"(n));
+        return n;
+    };
+    auto own = [&](int r) __attribute__((always_inline)) -> double * { return stage + (wave * R + r) * SROW; };
     const int grp = lane >> 4, col = lane & 15;  // matrix-step lane coordinates
-    const WaveLds<R> lds{wareas + wave * Cfg::WD};
 
-    // acc[r][c] = sum_d X_m[d] T_j[d] for this wave's rows m and key blocks
-    // j = lane + 64 c, with X_m vector `xs` of row m and T the head's pooled tensor
-    // behind rs. Tiles of 16 key blocks go round the waves; for tile t, lane l holds
-    // channels 16 (l / 16) .. +15 of key block 16 t + l % 16 (in step s the k index
-    // l / 16 stands for channel 16 (l / 16) + s, in A as in B) and the tile is
-    // multiplied with every 16-row tile of the workgroup (rows past RW repeat the
-    // last one; their results are not read). Results reach the owners through the
-    // staging area, CHK slots at a time.
-    auto dot_pass = [&](int xs, __amdgpu_buffer_rsrc_t rs, double (&acc)[R][CPL]) __attribute__((always_inline)) {
-        const double *arow[MT];
+    // Tile t of a pooled tensor (16 key blocks; zero past its end): lane l holds, of key
+    // block 16 t + l % 16, channels 8 u + 2 (l / 16) + e (u < 8, e = 0, 1) as b[2 u + e].
+    // Loaded as they lie, a lane's neighbours would hold other key blocks and each load
+    // take the L1 one cycle a lane (measured at 1,074 key blocks: a pass took 35 K cycles,
+    // all of it these loads, with half as much matrix work). So four lanes read 64
+    // contiguous bytes of a key block (lane l: block l / 4, 16 bytes l % 4) and the wave
+    // exchanges them in 512 bytes of LDS of its own, `buf` (a wave's LDS accesses are in
+    // order); the odd half of the blocks swaps its 16-byte pairs, so that the reads are
+    // free of conflicts.
+    auto load_tile = [&](__amdgpu_buffer_rsrc_t rs, int t, double *buf, double (&b)[16])
+                         __attribute__((always_inline)) {
+        const int off = (16 * t + (lane >> 2)) * kD * (int)sizeof(double) + (lane & 3) * 16;
+        double *put = buf + ((lane & ~3) | ((lane & 3) ^ ((lane >> 5) << 1)));
+        const double *get = buf + 4 * col + (grp ^ ((col >> 3) << 1));
+        double2 v[8];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) arow[mt] = row_vec(xs, min(16 * mt + col, RW - 1)) + 16 * grp;
+        for (int u = 0; u < 8; ++u) v[u] = pooled_16(rs, off + 64 * u);
 #pragma unroll
-        for (int q = 0; q < NCH; ++q) {
-            const int t0 = 4 * CHK * q, t1 = min(4 * CHK * (q + 1), ntiles);
-            // Tile t belongs to wave t mod NW (loads past the tensor give zero).
-            auto load_b = [&](int t, double (&b)[16]) __attribute__((always_inline)) {
-                const int off = (16 * t + col) * kD * (int)sizeof(double) + grp * 128;
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const double2 v = pooled_16(rs, off + 16 * u);
-                    b[2 * u] = v.x;
-                    b[2 * u + 1] = v.y;
-                }
-            };
-            for (int t = t0 + (wave - t0 % NW + NW) % NW; t < t1; t += NW) {
-                double b[16];
-                load_b(t, b);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    v4d c = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const double2 a = *reinterpret_cast<const double2 *>(arow[mt] + 2 * u);
-                        c = mfma_f64(a.x, b[2 * u], c);
-                        c = mfma_f64(a.y, b[2 * u + 1], c);
-                    }
-                    // c[v] = C[16 mt + 4 v + l / 16][16 t + l % 16]
-                    double *dst = stage + (16 * mt + grp) * SROW + (16 * t - 64 * CHK * q) + col;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) dst[4 * v * SROW] = c[v];
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int c = 0; c < CPL; ++c)
-                if (c / CHK == q)
-#pragma unroll
-                    for (int r = 0; r < R; ++r) acc[r][c] = stage[(wave * R + r) * SROW + (c - CHK * q) * 64 + lane];
-            __syncthreads();
+        for (int u = 0; u < 8; ++u) {
+            *put = v[u].x;
+            __builtin_amdgcn_wave_barrier();
+            b[2 * u] = *get;
+            __builtin_amdgcn_wave_barrier();
+            *put = v[u].y;
+            __builtin_amdgcn_wave_barrier();
+            b[2 * u + 1] = *get;
+            __builtin_amdgcn_wave_barrier();
         }
     };
-    // out_m[d] = sum_j w_m(j) Vbar_j[d] for every row m of the workgroup, into vector
-    // `os` of row m, with w_m(j) = w[r][c] of the owning wave (zero for key blocks
-    // past n_kb). The owners stage their weights CHK slots at a time. Item
-    // (mt, np, ks) of wave mt 2 KS + np KS + ks accumulates the 16 rows of tile mt
-    // against channels 32 np + 2 n + e (n < 16, e = 0, 1) over the key-block
-    // octets o = ks (mod KS): in each step the k index l / 16 stands for key block
-    // 8 o + 2 (l / 16) + (0 or 1), so one 16-byte read gives the A values of two
-    // steps and one 16-byte read of a key block's channel pair the B values of two
-    // products. The KS partial tiles are then added in split order by the owners.
-    auto wsum_pass = [&](const double (&w)[R][CPL], int os) __attribute__((always_inline)) {
+    auto buf_of = [&](int slot) __attribute__((always_inline)) -> double * { return row_vec(slot, 0) + 64 * wave; };
+    // Products of every row's vector `xs` with the 16 key blocks of tile t, into the
+    // staging rows (in step 2 u + e the k index l / 16 stands for channel
+    // 8 u + 2 (l / 16) + e, in A as in B; rows past RW repeat the last one and are not
+    // stored).
+    auto tile_product = [&](int xs, int t, const double (&b)[16]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const double *arow = row_vec(xs, min(16 * mt + col, RW - 1)) + 2 * grp;
+            v4d c = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const double2 a = *reinterpret_cast<const double2 *>(arow + 8 * u);
+                c = mfma_f64(a.x, b[2 * u], c);
+                c = mfma_f64(a.y, b[2 * u + 1], c);
+                if (Cfg::FENCE > 0 && u % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+            }
+            // c[v] = C[16 mt + 4 v + l / 16][16 t + l % 16]
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int m = 16 * mt + 4 * v + grp;
+                if (RW % 16 == 0 || m < RW) stage[m * SROW + 16 * t + col] = c[v];
+            }
+        }
+    };
+    // stage[m][j] = X_m . T_j for the workgroup's rows m and key blocks j, X_m vector
+    // `xs` of row m, T the head's pooled tensor behind rs. Tile t belongs to wave
+    // t mod NW; its first VT tiles come from the registers `res`. The caller has
+    // every row's vector in place and nobody reading the staging rows; ends with a
+    // barrier, after which the owners read their rows.
+    auto dot_pass = [&](int xs, __amdgpu_buffer_rsrc_t rs, const double (&res)[VT > 0 ? VT : 1][16])
+                        __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < VT; ++i)
+            if (wave + NW * i < ntiles) tile_product(xs, wave + NW * i, res[i]);
+        if constexpr (TPW > VT) {
+#pragma unroll 1
+            for (int t = wave + NW * VT; t < ntiles; t += NW) {
+                double b[16];
+                load_tile(rs, t, buf_of(xs ^ 1), b);  // in the vector slot not in use
+                tile_product(xs, t, b);
+            }
+        }
+        __syncthreads();
+    };
+    // out_m[d] = sum_j w_m(j) Vbar_j[d] for every row m of the workgroup, with w_m(j) =
+    // w(r, c) of the owning wave (zero for key blocks past n_kb): vector slot 0 of row m,
+    // and out[r] = channel `lane` of the wave's rows. The owners stage their weights.
+    // Item (mt, np, ks) of wave mt 2 KS + np KS + ks accumulates the 16 rows of tile mt
+    // against channels 32 np + 2 n + e (n < 16, e = 0, 1) over the key-block octets
+    // o = ks (mod KS): in each step the k index l / 16 stands for key block
+    // 8 o + 2 (l / 16) + (0 or 1), so one 16-byte read gives the A values of two steps
+    // and one 16-byte read of a key block's channel pair the B values of two products.
+    // The KS partial tiles are then added in split order by the owners. Ends with a
+    // barrier.
+    auto wsum_pass = [&](auto w, double (&out)[R]) __attribute__((always_inline)) {
         const bool mine = wave < 2 * MT * KS;
         const int it = mine ? wave : 0;
         const int ks = it % KS, np = (it / KS) & 1, mt = it / (2 * KS);
         v4d c0 = {0.0, 0.0, 0.0, 0.0}, c1 = c0;
-        const double *arow = stage + (16 * mt + col) * SROW + 2 * grp;
-        const int boff = (32 * np + 2 * col) * (int)sizeof(double);
 #pragma unroll
-        for (int q = 0; q < NCH; ++q) {
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int c = 0; c < CPL; ++c)
-                if (c / CHK == q)
+            for (int c = 0; c < CPL; ++c) own(r)[c * 64 + lane] = w(r, c);
+        __syncthreads();
+        if (mine) {
+            const double *arow = stage + min(16 * mt + col, RW - 1) * SROW + 2 * grp;
+            const int boff = (32 * np + 2 * col) * (int)sizeof(double) + 2 * grp * kD * (int)sizeof(double);
+            const int noct = (nkb + 7) >> 3;
+            // Four octets at a time (weights and pooled rows past the last block are zero
+            // or read as zero, the staged row reaches 64 CPL blocks).
+            for (int o = ks; o < noct; o += 4 * KS) {
+                double2 a[4], b0[4], b1[4];
 #pragma unroll
-                    for (int r = 0; r < R; ++r) stage[(wave * R + r) * SROW + (c - CHK * q) * 64 + lane] = w[r][c];
-            __syncthreads();
-            const int kq = min(64 * CHK, nkb - 64 * CHK * q);  // key blocks of the chunk
-            if (mine && kq > 0) {
-                const int noct = (kq + 7) >> 3;
-                const int key0 = 64 * CHK * q + 2 * grp;
-#pragma unroll 4
-                for (int o = ks; o < noct; o += KS) {
-                    const double2 a = *reinterpret_cast<const double2 *>(arow + 8 * o);
-                    const int key = key0 + 8 * o;
-                    const double2 b0 = pooled_16(rsV, key * kD * (int)sizeof(double) + boff);
-                    const double2 b1 = pooled_16(rsV, (key + 1) * kD * (int)sizeof(double) + boff);
-                    c0 = mfma_f64(a.x, b0.x, c0);
-                    c1 = mfma_f64(a.x, b0.y, c1);
-                    c0 = mfma_f64(a.y, b1.x, c0);
-                    c1 = mfma_f64(a.y, b1.y, c1);
+                for (int u = 0; u < 4; ++u) {
+                    const int ou = o + u * KS, off = 8 * ou * kD * (int)sizeof(double) + boff;
+                    b0[u] = pooled_16(rsV, off);
+                    b1[u] = pooled_16(rsV, off + kD * (int)sizeof(double));
+                    a[u] = *reinterpret_cast<const double2 *>(arow + 8 * min(ou, noct - 1));
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const bool in = o + u * KS < noct;  // wave-uniform
+                    if (!in) break;
+                    c0 = mfma_f64(a[u].x, b0[u].x, c0);
+                    c1 = mfma_f64(a[u].x, b0[u].y, c1);
+                    c0 = mfma_f64(a[u].y, b1[u].x, c0);
+                    c1 = mfma_f64(a[u].y, b1[u].y, c1);
                 }
             }
-            __syncthreads();
         }
+        __syncthreads();
         // c_e[v] = partial of row 16 mt + 4 v + l / 16, channel 32 np + 2 (l % 16) + e
         if (mine) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                double *o = stage + (16 * mt + 4 * v + grp) * SROW + ks * kD + 32 * np + 2 * col;
-                *reinterpret_cast<double2 *>(o) = double2{c0[v], c1[v]};
+                const int m = 16 * mt + 4 * v + grp;
+                if (RW % 16 == 0 || m < RW)
+                    *reinterpret_cast<double2 *>(stage + m * SROW + ks * kD + 32 * np + 2 * col) =
+                        double2{c0[v], c1[v]};
             }
         }
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const double *src = stage + (wave * R + r) * SROW + lane;
+            const double *src = own(r) + lane;
             double tot = src[0];
 #pragma unroll
             for (int k2 = 1; k2 < KS; ++k2) tot += src[k2 * kD];
-            lds.vec(os, r)[lane] = tot;
+            out[r] = tot;
         }
-        __syncthreads();
     };
 
-    // x_m = A y_m for every row m of the workgroup (y: vector `ys`, x: vector `xs`)
+    // x_m = A y_m for every row m of the workgroup (y: vector slot 0, x: vector slot 1)
     // with A = M_h, or with SYM its symmetric part (M + M^T) / 2 (the same quadratic
     // form; exact in float64 from float32 entries). Item (mt, nt) of 4 MT, on
     // wave mt 4 + nt: the 16 rows of tile mt against output channels 16 nt .. +15,
-    // k <-> channel 16 (l / 16) + s in step s as in dot_pass; B from M_h in LDS.
-    // Ends with a workgroup barrier (the owners then read x).
-    auto mv_pass = [&](auto sym, int ys, int xs) __attribute__((always_inline)) {
+    // k <-> channel 16 u + 4 (l / 16) + e in step 4 u + e. Begins and ends with
+    // a barrier (the owners write y before and read x after).
+    auto mv_pass = [&](auto sym) __attribute__((always_inline)) {
         constexpr bool SYM = decltype(sym)::value;
+        __syncthreads();
         if (wave < 4 * MT) {
             const int mt = wave >> 2, nt = wave & 3;
-            const double *arow = row_vec(ys, min(16 * mt + col, RW - 1)) + 16 * grp;
+            const double *arow = row_vec(0, min(16 * mt + col, RW - 1)) + 4 * grp;
             const int n = 16 * nt + col;
             v4d c = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const double2 a = *reinterpret_cast<const double2 *>(arow + 2 * u);
-                const int k = 16 * grp + 2 * u;
-                double b0 = (double)Ms[n * (kD + 1) + k], b1 = (double)Ms[n * (kD + 1) + k + 1];
-                if (SYM) {
-                    b0 = 0.5 * (b0 + (double)Ms[k * (kD + 1) + n]);
-                    b1 = 0.5 * (b1 + (double)Ms[(k + 1) * (kD + 1) + n]);
+            for (int u = 0; u < 4; ++u) {
+                const int k = 16 * u + 4 * grp;
+                const double2 a0 = *reinterpret_cast<const double2 *>(arow + 16 * u);
+                const double2 a1 = *reinterpret_cast<const double2 *>(arow + 16 * u + 2);
+                const double a[4] = {a0.x, a0.y, a1.x, a1.y};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    double b = m_at(n, k + e);
+                    if (SYM) b = 0.5 * (b + m_at(k + e, n));
+                    c = mfma_f64(a[e], b, c);
                 }
-                c = mfma_f64(a.x, b0, c);
-                c = mfma_f64(a.y, b1, c);
             }
             // c[v] = x[row 16 mt + 4 v + l / 16][channel n]
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int m = 16 * mt + 4 * v + grp;
-                if (m < RW) row_vec(xs, m)[n] = c[v];
+                if (RW % 16 == 0 || m < RW) row_vec(1, m)[n] = c[v];
             }
         }
         __syncthreads();
@@ -612,129 +578,100 @@ __global__ void __launch_bounds__(NW * 64, 1) select_kernel(const SelectParams p
 
     int irow[R];
     bool live[R], dense[R];
-    double *vbv[R], *wvv[R], *gv[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         live[r] = row0 + r < nqb;
         irow[r] = live[r] ? row0 + r : nqb - 1;
-        dense[r] = irow[r] >= p.first_dense_qb || c_h >= n_p;
-        vbv[r] = lds.vec(0, r);
-        wvv[r] = lds.vec(1, r);
-        gv[r] = lds.vec(2, r);
-        vbv[r][lane] = p.pooled.qbar[((size_t)h * nqb + irow[r]) * kD + lane];  // Qbar_i for now
+        dense[r] = !live[r] || irow[r] >= p.first_dense_qb || c_h >= n_p;
     }
-    int jc[CPL];  // this lane's key block per slot, clamped into range for reads
-    bool valid[CPL];
-    unsigned long long cand_bits = 0;  // bit c: slot c of this lane is a candidate
+    using bits = typename Cfg::bits;  // one bit per slot of this lane
+    bits cand_bits = 0;               // bit c: slot c is a candidate
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-        const int j = lane + 64 * c;
-        valid[c] = j < nkb;
-        jc[c] = valid[c] ? j : nkb - 1;
-        if (j < n_p) cand_bits |= 1ull << c;
+    for (int c = 0; c < CPL; ++c)
+        if (lane + 64 * c < n_p) cand_bits |= (bits)1 << c;
+
+    double res[VT > 0 ? VT : 1][16];  // this wave's resident tiles: Kbar, then Vbar
+    {
+        constexpr int T = NW * 64, M4 = M_LDS ? (kD * kD / 4 + T - 1) / T : 1;
+        float4 mreg[M4];
+        double qreg[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) qreg[r] = p.pooled.qbar[((size_t)h * nqb + irow[r]) * kD + lane];
+        if (M_LDS)
+#pragma unroll
+            for (int u = 0; u < M4; ++u)
+                mreg[u] = reinterpret_cast<const float4 *>(Mh)[min(u * T + tid, kD * kD / 4 - 1)];
+#pragma unroll
+        for (int i = 0; i < VT; ++i) load_tile(rsK, wave + NW * i, buf_of(1), res[i]);
+#pragma unroll
+        for (int r = 0; r < R; ++r) row_vec(0, wave * R + r)[lane] = qreg[r];
+        if (M_LDS)
+#pragma unroll
+            for (int u = 0; u < M4; ++u) {
+                const int e = 4 * (u * T + tid);
+                if (e < kD * kD) {
+                    float *dst = Ms + (e >> 6) * (kD + 1) + (e & 63);
+                    dst[0] = mreg[u].x;
+                    dst[1] = mreg[u].y;
+                    dst[2] = mreg[u].z;
+                    dst[3] = mreg[u].w;
+                }
+            }
     }
     __syncthreads();  // M_h and every row's Qbar in place
 
-    // Pooled logits Qbar_i . Kbar_j / sqrt(D) (Eq. 1).
-    double acc[R][CPL], P[R][CPL], S2[R][CPL];
-    dot_pass(0, rsK, acc);
-    // Softmax over all key blocks.
+    // Pooled logits Qbar_i . Kbar_j / sqrt(D) (Eq. 1), softmax over all key blocks.
+    dot_pass(0, rsK, res);
+#pragma unroll
+    for (int i = 0; i < VT; ++i) load_tile(rsV, wave + NW * i, buf_of(1), res[i]);
+    double P[R][CPL], S2[R][CPL];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
+        const int nkb = nkb_here();
         double mx = -INFINITY;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-            acc[r][c] *= 0.125;  // 1/sqrt(64)
-            if (valid[c]) mx = fmax(mx, acc[r][c]);
+            P[r][c] = own(r)[c * 64 + lane] * 0.125;  // 1/sqrt(64)
+            if (lane + 64 * c < nkb) mx = fmax(mx, P[r][c]);
         }
         mx = wave_max(mx);
         double z = 0.0;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-            P[r][c] = valid[c] ? exp(acc[r][c] - mx) : 0.0;
+            P[r][c] = lane + 64 * c < nkb ? exp(P[r][c] - mx) : 0.0;
             z += P[r][c];
+            slot_fence(c);
         }
         z = wave_sum(z);
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) P[r][c] = P[r][c] / z;
+        for (int c = 0; c < CPL; ++c) {
+            P[r][c] = P[r][c] / z;
+            slot_fence(c);
+        }
         if (p.prob_out && live[r]) {
+            const int nkb = nkb_here();
             double *po = p.prob_out + ((size_t)h * nqb + irow[r]) * nkb;
 #pragma unroll
             for (int c = 0; c < CPL; ++c)
-                if (valid[c]) po[lane + 64 * c] = P[r][c];
+                if (lane + 64 * c < nkb) po[lane + 64 * c] = P[r][c];
         }
     }
 
-    // Dense pooled output vbar_i = sum_j P_ij Vbar_j (over Qbar_i, no longer
-    // needed), w_i = S vbar_i with S the symmetric part of M (lane <-> channel),
-    // and vbar_i^T S vbar_i.
-    double vsv[R];
-    {
-        wsum_pass(P, 0);
-        mv_pass(sym_mv{}, 0, 1);  // every row's w in place
+    // Dense pooled output vbar_i = sum_j P_ij Vbar_j, w_i = S vbar_i with S the symmetric
+    // part of M (lane <-> channel), and vbar_i^T S vbar_i.
+    double vb[R], vsv[R];
+    wsum_pass([&](int r, int c) { return P[r][c]; }, vb);
 #pragma unroll
-        for (int r = 0; r < R; ++r) vsv[r] = wave_sum(vbv[r][lane] * wvv[r][lane]);
-    }
+    for (int r = 0; r < R; ++r) row_vec(0, wave * R + r)[lane] = vb[r];
+    mv_pass(sym_mv{});
+#pragma unroll
+    for (int r = 0; r < R; ++r) vsv[r] = wave_sum(vb[r] * row_vec(1, wave * R + r)[lane]);
 
     // q_ij = e^T M e with e = vbar_i - Vbar_j (Eq. 9), expanded through the symmetric
     // part S of M (same quadratic form): q = vbar_i^T S vbar_i - 2 Vbar_j . w_i +
     // Vbar_j^T M Vbar_j, the last term per block from the pooling pass.
     // s_ij = P_ij sqrt(q_ij), key_ij = s_ij / max(1 - P_ij, eps) (Eqs. 6-7).
-    double cj[CPL];
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) cj[c] = cT[jc[c]];
-    dot_pass(1, rsV, acc);
-    // The block with P > 1/2, if a row has one (at most one does): there e = vbar_i -
-    // Vbar_j shrinks with 1 - P while the expansion's terms do not, so the expansion
-    // would leave mostly rounding error (a single-block row: e = 0 exactly). Its q is
-    // taken directly as e^T M e (M_h from LDS; e through the wave's staging rows, idle
-    // after the product): lane t forms e_t (M e)_t.
-    int dom_c[R], dom_l[R];
-    double q_dom[R];
-    {
-        double *ebuf = stage + (size_t)wave * R * SROW;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            dom_c[r] = -1;
-            dom_l[r] = 0;
-            q_dom[r] = 0.0;
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-                const unsigned long long b = __ballot(valid[c] && P[r][c] > 0.5);
-                if (b != 0ull) {
-                    dom_c[r] = c;
-                    dom_l[r] = __builtin_ctzll(b);
-                }
-            }
-            if (dom_c[r] < 0) continue;
-            const double e = vbv[r][lane] - pooled_row(rsV, dom_l[r] + 64 * dom_c[r], lane);
-            ebuf[lane] = e;
-            __builtin_amdgcn_wave_barrier();
-            double u = 0.0;
-            for (int c = 0; c < kD; ++c) u = fma((double)Ms[lane * (kD + 1) + c], ebuf[c], u);
-            __builtin_amdgcn_wave_barrier();
-            q_dom[r] = wave_sum(e * u);
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) {
-            const double q = (c == dom_c[r] && lane == dom_l[r]) ? q_dom[r] : fma(-2.0, acc[r][c], vsv[r] + cj[c]);
-            const double s = P[r][c] * sqrt(q > 0.0 ? q : 0.0);
-            const double den = 1.0 - P[r][c];
-            S2[r][c] = s * s;
-            acc[r][c] = s / (den > eps ? den : eps);  // ranking key
-        }
-        if (p.key_out && live[r]) {
-            double *ko = p.key_out + ((size_t)h * nqb + irow[r]) * nkb;
-#pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-                const int j = lane + 64 * c;
-                if (valid[c]) ko[j] = j < n_p ? acc[r][c] : -1.0;
-            }
-        }
-    }
+    dot_pass(1, rsV, res);
 
     // Initial selection (Eq. 7), then the state of each drop set (Eqs. 10-12):
     // g = sum_{j in D} P_j (vbar - Vbar_j), K = 1 - sum_{j in D} P_j, G = g^T M g.
@@ -744,43 +681,98 @@ __global__ void __launch_bounds__(NW * 64, 1) select_kernel(const SelectParams p
     // whose mass, forced blocks included, reaches cdf_tau.
     const int crit = p.criterion;
     const bool maximise = crit == RESS_CRITERION_DRIFT_MAX_SWAP || crit == RESS_CRITERION_DRIFT_MAX_FULL;
-    unsigned long long inD[R], best[R];
-    double K[R], G[R], J[R], J0[R], Jb[R], msum[R];
+    const bool capped = crit == RESS_CRITERION_PROBABILITY && p.cdf_tau > 0.0;
+    bits inD[R], best[R];
+    double K[R], G[R], J[R], Jb[R], msum[R];  // wave-uniform
     int crow[R];  // kept candidates of the row
+    // Order keys go into the row's staging row (this lane's slots only).
+    auto put_key = [&](int r, int c, double x) __attribute__((always_inline)) {
+        own(r)[c * 64 + lane] = __longlong_as_double((long long)order_key(x));
+    };
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        inD[r] = 0ull;
+        double acc[CPL];
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) acc[c] = own(r)[c * 64 + lane];
+        // The block with P > 1/2, if a row has one (at most one does): there e = vbar_i -
+        // Vbar_j shrinks with 1 - P while the expansion's terms do not, so the expansion
+        // would leave mostly rounding error (a single-block row: e = 0 exactly). Its q is
+        // taken directly as e^T M e (e through the row's staging row, read out above):
+        // lane t forms e_t (M e)_t.
+        const int nkb = nkb_here();
+        int dom_c = -1, dom_l = 0;
+        double q_dom = 0.0;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            const unsigned long long b = __ballot(lane + 64 * c < nkb && P[r][c] > 0.5);
+            if (b != 0ull) {
+                dom_c = c;
+                dom_l = __builtin_ctzll(b);
+            }
+        }
+        if (dom_c >= 0) {
+            double *ebuf = own(r);
+            const double e = vb[r] - pooled_row(rsV, dom_l + 64 * dom_c, lane);
+            __builtin_amdgcn_wave_barrier();
+            ebuf[lane] = e;
+            __builtin_amdgcn_wave_barrier();
+            double u = 0.0;
+            for (int c = 0; c < kD; ++c) u = fma(m_at(lane, c), ebuf[c], u);
+            __builtin_amdgcn_wave_barrier();
+            q_dom = wave_sum(e * u);
+        }
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+            const double cj = cT[min(lane + 64 * c, nkb - 1)];
+            const double q = (c == dom_c && lane == dom_l) ? q_dom : fma(-2.0, acc[c], vsv[r] + cj);
+            const double s = P[r][c] * sqrt(q > 0.0 ? q : 0.0);
+            const double den = 1.0 - P[r][c];
+            S2[r][c] = s * s;
+            acc[c] = s / (den > eps ? den : eps);  // ranking key
+            slot_fence(c);
+        }
+        if (p.key_out && live[r]) {
+            const int nkb = nkb_here();
+            double *ko = p.key_out + ((size_t)h * nqb + irow[r]) * nkb;
+#pragma unroll
+            for (int c = 0; c < CPL; ++c) {
+                const int j = lane + 64 * c;
+                if (j < nkb) ko[j] = j < n_p ? acc[c] : -1.0;
+            }
+        }
+        inD[r] = 0;
         crow[r] = c_h;
         if (!dense[r]) {
-            unsigned long long ko[CPL];
 #pragma unroll
             for (int c = 0; c < CPL; ++c)
-                ko[c] = order_key(crit == RESS_CRITERION_PROBABILITY ? P[r][c]
-                                  : crit == RESS_CRITERION_DRIFT_MAX_FULL ? -acc[r][c] : acc[r][c]);
-            if (crit == RESS_CRITERION_PROBABILITY && p.cdf_tau > 0.0) {
+                put_key(r, c, crit == RESS_CRITERION_PROBABILITY ? P[r][c]
+                              : crit == RESS_CRITERION_DRIFT_MAX_FULL ? -acc[c] : acc[c]);
+            const double *keys = own(r) + lane;
+            if (capped) {
                 // mass(n) = forced mass + the n largest candidate P: smallest n <= c_h
                 // with mass(n) >= tau by bisection (mass is non-decreasing in n).
+                const int nkb = nkb_here();
                 double fm = 0.0;
 #pragma unroll
                 for (int c = 0; c < CPL; ++c) {
                     const int j = lane + 64 * c;
-                    if (valid[c] && j >= n_p) fm += P[r][c];
+                    if (j < nkb && j >= n_p) fm += P[r][c];
                 }
                 fm = wave_sum(fm);
                 auto mass = [&](int n) {
-                    const unsigned long long sel = topk_slots<CPL>(ko, cand_bits, n, lane_lt);
+                    const bits sel = topk_slots<CPL>(keys, cand_bits, n, lane_lt);
                     double m = 0.0;
 #pragma unroll
                     for (int c = 0; c < CPL; ++c)
-                        if ((sel >> c) & 1ull) m += P[r][c];
+                        if ((sel >> c) & 1) m += P[r][c];
                     return fm + wave_sum(m);
                 };
-                int lo = 0, hi = c_h;
-                if (mass(hi) >= p.cdf_tau) {
-                    while (lo < hi) {
-                        const int mid = (lo + hi) >> 1;
+                int lo = 0, hi_n = c_h;
+                if (mass(hi_n) >= p.cdf_tau) {
+                    while (lo < hi_n) {
+                        const int mid = (lo + hi_n) >> 1;
                         if (mass(mid) >= p.cdf_tau)
-                            hi = mid;
+                            hi_n = mid;
                         else
                             lo = mid + 1;
                     }
@@ -788,95 +780,118 @@ __global__ void __launch_bounds__(NW * 64, 1) select_kernel(const SelectParams p
                     crow[r] = max(lo, min(floor2, n_p));
                 }
             }
-            const unsigned long long keep = topk_slots<CPL>(ko, cand_bits, crow[r], lane_lt);
+            const bits keep = topk_slots<CPL>(keys, cand_bits, crow[r], lane_lt);
             inD[r] = cand_bits & ~keep;
         }
         double mass = 0.0;
 #pragma unroll
-        for (int c = 0; c < CPL; ++c) {
-            acc[r][c] = ((inD[r] >> c) & 1ull) ? P[r][c] : 0.0;  // weights of the g pass
-            mass += acc[r][c];
-        }
+        for (int c = 0; c < CPL; ++c) mass += ((inD[r] >> c) & 1) ? P[r][c] : 0.0;
         msum[r] = wave_sum(mass);
-        K[r] = 1.0 - msum[r];
+        K[r] = uniform(1.0 - msum[r]);
     }
     // g = sum_{j in D} P_j (vbar - Vbar_j) = (sum_{j in D} P_j) vbar - sum_{j in D} P_j Vbar_j
-    wsum_pass(acc, 2);
+    double gr[R];
+    wsum_pass([&](int r, int c) { return ((inD[r] >> c) & 1) ? P[r][c] : 0.0; }, gr);
 #pragma unroll
-    for (int r = 0; r < R; ++r) gv[r][lane] = fma(msum[r], vbv[r][lane], -gv[r][lane]);
-    double *hv[R];  // M g reuses the slot of S vbar
-#pragma unroll
-    for (int r = 0; r < R; ++r) hv[r] = wvv[r];
+    for (int r = 0; r < R; ++r) gr[r] = fma(msum[r], vb[r], -gr[r]);
     // h = M g, G = g . h, J = G / max(K, eps)^2, and vbar . h for the next round's gains.
     double vmg[R];
-    auto objective = [&]() {
-        __syncthreads();  // every row's g in place
-        mv_pass(plain_mv{}, 2, 1);
+    auto objective = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) row_vec(0, wave * R + r)[lane] = gr[r];
+        mv_pass(plain_mv{});
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const double hh = hv[r][lane];
-            wave_sum2(gv[r][lane] * hh, vbv[r][lane] * hh, G[r], vmg[r]);
+            const double hh = row_vec(1, wave * R + r)[lane];
+            wave_sum2(gr[r] * hh, vb[r] * hh, G[r], vmg[r]);
             const double Kh = K[r] > eps ? K[r] : eps;
-            J[r] = G[r] / (Kh * Kh);
+            J[r] = uniform(G[r] / (Kh * Kh));
+            G[r] = uniform(G[r]);
+            vmg[r] = uniform(vmg[r]);
         }
     };
     objective();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        J0[r] = Jb[r] = J[r];
+        Jb[r] = J[r];
+        if (p.drift && live[r] && lane == 0) p.drift[2 * ((size_t)h * nqb + irow[r])] = J[r];
         best[r] = inD[r];
     }
 
     // Budget-neutral restoration rounds (Eqs. 13-17) with track-best. The swap
     // count follows each row's kept count; the workgroup stops once no row of it
-    // swaps anything.
-    double *swap_w = lds.swap_w();
-    int *swap_j = lds.swap_j();
-    // The wave's own staging rows, idle between the products: scratch for packing
-    // sparse member sets in the searches.
-    unsigned int *scr = reinterpret_cast<unsigned int *>(stage + (size_t)wave * R * SROW);
+    // swaps anything (the rows that are not dense keep c_h candidates each, unless a
+    // CDF cap makes the counts differ).
+    auto swaps = [&](int kept, double share) {  // share = rho 2^-(r+1) of round r (Eq. 17)
+        return min(max((int)floor(share * (double)kept), p.swap_floor), min(n_p - kept, kept));
+    };
+    const bool any_row = (item % groups) * RW < p.first_dense_qb && c_h < n_p;
+    double share = p.rho;
     for (int rr = 0; rr < p.rounds; ++rr) {
-        int mrow[R], mmax = 0;
+        share *= 0.5;
+        const int m_all = __builtin_amdgcn_readfirstlane(swaps(c_h, share));
+        if (capped) {
+            int mmax = 0;
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int m = swaps_of_round(crow[r], p.rho, rr, p.swap_floor);
-            mrow[r] = dense[r] ? 0 : min(m, min(n_p - crow[r], crow[r]));
-            mmax = max(mmax, mrow[r]);
+            for (int r = 0; r < R; ++r)
+                if (!dense[r]) mmax = max(mmax, swaps(crow[r], share));
+            if (lane == 0) flags[wave] = mmax;
+            __syncthreads();
+            mmax = 0;
+            for (int w = 0; w < NW; ++w) mmax = max(mmax, flags[w]);
+            __syncthreads();
+            if (mmax <= 0) break;
+        } else if (!any_row || m_all <= 0) {
+            break;
         }
-        if (!__syncthreads_or(mmax > 0)) break;
-        // e_k . (M g) = vbar . (M g) - Vbar_k . (M g) for every candidate k of every row.
-        dot_pass(1, rsV, acc);
+        // (Negated copies of P are formed where they are used, not kept over the rounds.)
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) acc[r][c] = vmg[r] - acc[r][c];
+            for (int c = 0; c < CPL; ++c) asm("" : "+v"(P[r][c]));
+        // e_k . (M g) = vbar . (M g) - Vbar_k . (M g) for every candidate k of every row.
+        dot_pass(1, rsV, res);
         // Gains of every single restore / drop at the round-start state; the m best
         // of each kind are applied together, g and K following Eq. 13.
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int m = mrow[r];
+            const int m = dense[r] ? 0 : (capped ? swaps(crow[r], share) : m_all);
             if (m <= 0) continue;
-            unsigned long long dj[CPL];
+            // Eqs. 14-16 with P_k negated for the blocks outside the drop set:
+            // dG = -2 P_k e_k . (M g) + s_k^2, K' = K + P_k, dJ = J - (G + dG) / max(K', eps)^2.
+            auto gains = [&](auto quotient) __attribute__((always_inline)) {
 #pragma unroll
-            for (int c = 0; c < CPL; ++c) {
-                const bool in = (inD[r] >> c) & 1ull;
-                const double dkMg = P[r][c] * acc[r][c];
-                const double dG = in ? -2.0 * dkMg + S2[r][c] : 2.0 * dkMg + S2[r][c];  // Eqs. 14-15
-                const double Kn = K[r] + (in ? P[r][c] : -P[r][c]);
-                const double Knh = Kn > eps ? Kn : eps;
-                const double dJ = J[r] - (G[r] + dG) / (Knh * Knh);  // Eq. 16
-                dj[c] = order_key(maximise ? -dJ : dJ);
-            }
-            const unsigned long long rest = topk_any<CPL>(dj, inD[r], m, lane, lane_lt, scr);
-            const unsigned long long drop = topk_any<CPL>(dj, cand_bits & ~inD[r], m, lane, lane_lt, scr);
+                for (int c = 0; c < CPL; ++c) {
+                    const double sp = ((inD[r] >> c) & 1) ? P[r][c] : -P[r][c];
+                    const double ek = vmg[r] - own(r)[c * 64 + lane];
+                    const double num = fma(-2.0 * sp, ek, G[r] + S2[r][c]);
+                    const double Kn = K[r] + sp;
+                    const double Knh = Kn > eps ? Kn : eps;
+                    const double dJ = J[r] - quotient(num, Knh * Knh);
+                    put_key(r, c, maximise ? -dJ : dJ);
+                    slot_fence(c);
+                }
+            };
+            if (eps >= 1e-100)
+                gains([](double x, double d) { return quot(x, d); });
+            else
+                gains([](double x, double d) { return x / d; });
+            const double *keys = own(r) + lane;
+            const bits rest = topk_slots<CPL>(keys, inD[r], m, lane_lt);
+            const bits drop = topk_slots<CPL>(keys, cand_bits & ~inD[r], m, lane_lt);
             inD[r] = (inD[r] & ~rest) | drop;
             double mr = 0.0, md = 0.0;
-            double g = gv[r][lane];
-            const double vbl = vbv[r][lane];
-            // The swapped blocks of all slots, in slot order, are gathered into one list
-            // (up to 64 entries) and applied 8 rows of Vbar at a time: restores
-            // subtract d_k, drops add it. The list is padded to a multiple of 8 with
+            // The swapped blocks, in slot order, are gathered into a list of (block, weight)
+            // pairs in the row's staging row (its keys are no longer needed; where the row
+            // might not hold them all, half of the slots at a time) and applied 8 rows of
+            // Vbar at a time: restores subtract d_k, drops add it. The list is padded to a multiple of 8 with
             // zero-weight entries of block 0, which leave g unchanged.
+            int lane_here = lane;  // block indices formed here, not kept per slot
+            asm("" : "+v"(lane_here));
+            constexpr int HALF = (CPL + 1) / 2;
+            static_assert((64 * HALF + 8) * 12 <= SROW * 8, "swap list");
+            double *swap_w = own(r);
+            int *swap_j = reinterpret_cast<int *>(own(r) + 64 * HALF + 8);
             int nbuf = 0;
             auto apply = [&]() __attribute__((always_inline)) {
                 const int nr = (nbuf + 7) & ~7;
@@ -884,44 +899,35 @@ __global__ void __launch_bounds__(NW * 64, 1) select_kernel(const SelectParams p
                     swap_j[nbuf + lane] = 0;
                     swap_w[nbuf + lane] = 0.0;
                 }
-                __builtin_amdgcn_wave_barrier();
+                asm volatile("" ::: "memory");
                 for (int t0 = 0; t0 < nr; t0 += 8) {
-                    const int4 ja = *reinterpret_cast<const int4 *>(swap_j + t0);
-                    const int4 jb = *reinterpret_cast<const int4 *>(swap_j + t0 + 4);
-                    const int js[8] = {ja.x, ja.y, ja.z, ja.w, jb.x, jb.y, jb.z, jb.w};
                     double vj[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) vj[u] = pooled_row(rsV, js[u], lane);
+                    for (int u = 0; u < 8; ++u) vj[u] = pooled_row(rsV, swap_j[t0 + u], lane);
 #pragma unroll
-                    for (int u = 0; u < 8; u += 2) {
-                        const double2 w = *reinterpret_cast<const double2 *>(swap_w + t0 + u);
-                        g = fma(w.x, vbl - vj[u], g);
-                        g = fma(w.y, vbl - vj[u + 1], g);
-                    }
+                    for (int u = 0; u < 8; ++u) gr[r] = fma(swap_w[t0 + u], vb[r] - vj[u], gr[r]);
                 }
-                __builtin_amdgcn_wave_barrier();
                 nbuf = 0;
+                asm volatile("" ::: "memory");
             };
+            asm volatile("" ::: "memory");  // the row changes its type
 #pragma unroll
             for (int c = 0; c < CPL; ++c) {
+                if (c == HALF && 2 * m > 64 * HALF) apply();  // the rest may not fit beside these
                 const bool is_rest = (rest >> c) & 1ull, is_drop = (drop >> c) & 1ull;
                 const unsigned long long sm = __ballot(is_rest || is_drop);
                 if (sm == 0ull) continue;
-                const int n = __popcll(sm);
-                if (nbuf + n > 64) apply();
                 if (is_rest || is_drop) {
                     const int pos = nbuf + __popcll(sm & lane_lt);
-                    swap_j[pos] = lane + 64 * c;
+                    swap_j[pos] = lane_here + 64 * c;
                     swap_w[pos] = is_drop ? P[r][c] : -P[r][c];
                 }
                 if (is_rest) mr += P[r][c];
                 if (is_drop) md += P[r][c];
-                nbuf += n;
+                nbuf += __popcll(sm);
             }
             if (nbuf > 0) apply();
-            K[r] += wave_sum(mr - md);
-            __builtin_amdgcn_wave_barrier();
-            gv[r][lane] = g;
+            K[r] = uniform(K[r] + wave_sum(mr - md));
         }
         objective();
 #pragma unroll
@@ -936,12 +942,13 @@ __global__ void __launch_bounds__(NW * 64, 1) select_kernel(const SelectParams p
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         if (!live[r]) continue;
+        const int nkb = nkb_here();
         const size_t row = (size_t)h * nqb + irow[r];
         int32_t *out = p.kept_idx + row * nkb;
         int before = 0;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
-            const bool kept = valid[c] && !((best[r] >> c) & 1ull);
+            const bool kept = lane + 64 * c < nkb && !((best[r] >> c) & 1);
             const unsigned long long km = __ballot(kept);
             if (kept) out[before + __popcll(km & lane_lt)] = lane + 64 * c;
             before += __popcll(km);
@@ -949,10 +956,7 @@ __global__ void __launch_bounds__(NW * 64, 1) select_kernel(const SelectParams p
         for (int t = before + lane; t < nkb; t += 64) out[t] = -1;
         if (lane == 0) {
             p.kept_count[row] = before;
-            if (p.drift) {
-                p.drift[2 * row] = J0[r];
-                p.drift[2 * row + 1] = Jb[r];
-            }
+            if (p.drift) p.drift[2 * row + 1] = Jb[r];
         }
     }
 }
@@ -967,31 +971,35 @@ hipError_t launch_cfg(const SelectParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
-// Rows per workgroup, among 24 (8 waves of 3 rows), 16 (8 waves of 2), 8 (8
-// waves of 1) and 4 (4 waves of 1): the one with the fewest rounds of
-// workgroups over the chip's 256 compute units (one workgroup each), weighted
-// by the rows each wave carries plus one (its serial row work); 4 rows over 8
-// on a tie (more compute units busy), and 16 or 24 only when strictly cheaper.
-// Several rows per wave only up to 6 slots per lane (their candidate state must
-// fit the registers of two waves per SIMD); 4 waves of 1 row beyond 1088 key
-// blocks.
+// Rows per workgroup: 4, 8, 12 or 16 waves of one row, or (up to 6 slots per lane) 12
+// waves of two, by the smallest number of rounds of workgroups over the chip's 256
+// compute units times the time of one workgroup. The latter were measured per round
+// over 8, 16, 32 and 100 views (us with 4 / 8 / 12 / 16 / 24 rows): 67 / 73 / 85 / 90 /
+// 158 at 344 key blocks, - / 129 / 140 / 158 at 687, - / 176 / 193 / 231 at 1,074; more
+// waves hide each other's latencies until they share the vector unit, more rows per
+// wave only add up. In hundredths of 8 rows: 90, 100, 112, 127, 210.
 constexpr long long kCUs = 256;
-template <int CPL, bool MULTI_ROW>
+template <int CPL>
 hipError_t launch_rows(const SelectParams &p, hipStream_t s)
 {
-    auto cost = [&](int rows, int r) {
+    auto cost = [&](int rows, int weight) {
         const long long wg = (long long)p.H * ((p.n_qb + rows - 1) / rows);
-        return ((wg + kCUs - 1) / kCUs) * (r + 1);
+        return ((wg + kCUs - 1) / kCUs) * weight;
     };
     int best = 8;
-    long long bc = cost(8, 1);
-    if (cost(4, 1) <= bc) best = 4, bc = cost(4, 1);
-    if constexpr (MULTI_ROW) {
-        if (cost(16, 2) < bc) best = 16, bc = cost(16, 2);
-        if (cost(24, 3) < bc) best = 24, bc = cost(24, 3);
-        if (best == 24) return launch_cfg<CPL, 3, 8>(p, s);
-        if (best == 16) return launch_cfg<CPL, 2, 8>(p, s);
+    long long bc = cost(8, 100);
+    auto consider = [&](int rows, int weight) {
+        if (cost(rows, weight) < bc) best = rows, bc = cost(rows, weight);
+    };
+    consider(4, 90);
+    consider(12, 112);
+    consider(16, 127);
+    if constexpr (CPL <= 6) {
+        consider(24, 210);
+        if (best == 24) return launch_cfg<CPL, 2, 12>(p, s);
     }
+    if (best == 16) return launch_cfg<CPL, 1, 16>(p, s);
+    if (best == 12) return launch_cfg<CPL, 1, 12>(p, s);
     if (best == 8) return launch_cfg<CPL, 1, 8>(p, s);
     return launch_cfg<CPL, 1, 4>(p, s);
 }
@@ -1002,13 +1010,14 @@ hipError_t launch_select(const SelectParams &p, hipStream_t s)
 {
     if (p.H == 0 || p.n_qb == 0) return hipSuccess;
     const int n = p.n_kb;
-    if (n <= 128) return launch_rows<2, true>(p, s);
-    if (n <= 256) return launch_rows<4, true>(p, s);
-    if (n <= 384) return launch_rows<6, true>(p, s);
-    if (n <= 512) return launch_rows<8, false>(p, s);
-    if (n <= 768) return launch_rows<12, false>(p, s);
-    if (n <= 1088) return launch_rows<17, false>(p, s);
-    if (n <= 2048) return launch_cfg<32, 1, 4>(p, s);
+    if (n <= 128) return launch_rows<2>(p, s);
+    if (n <= 256) return launch_rows<4>(p, s);
+    if (n <= 384) return launch_rows<6>(p, s);
+    if (n <= 512) return launch_rows<8>(p, s);
+    if (n <= 768) return launch_rows<12>(p, s);
+    if (n <= 1088) return launch_rows<17>(p, s);
+    if (n <= 1536) return launch_cfg<24, 1, 8>(p, s);
+    if (n <= 2304) return launch_cfg<36, 1, 8>(p, s);
     return launch_cfg<64, 1, 4>(p, s);
 }
 

@@ -219,7 +219,7 @@ int ress_select_noalloc(const ress_shape *shape, const ress_select_params *param
                        ws, (size_t)RESS_NOALLOC_SCRATCH_BYTES, stream);
 }
 
-// Shared checks of the two projections: shape, H a multiple of 4, grid size.
+// Shared checks of the two projections: shape, H a multiple of 4 (the grid fits 31 bits).
 static int proj_common(const ress_shape *shape, Grid *g, ress::ProjParams *pp, int n_out_per_head)
 {
     int st = check_shape(shape, g);
@@ -228,12 +228,7 @@ static int proj_common(const ress_shape *shape, Grid *g, ress::ProjParams *pp, i
     memset(pp, 0, sizeof *pp);
     pp->T = shape->N;
     pp->H = shape->H;
-    pp->m_tiles = (shape->N + 255) / 256;
-    pp->n_tiles = n_out_per_head * shape->H / 256;
-    const long long items = (long long)pp->m_tiles * pp->n_tiles;
-    const long long per_xcd = (items + 7) / 8;
-    if (8 * per_xcd > 0x7fffffffLL) return RESS_E_UNSUPPORTED;
-    pp->items_per_xcd = (int)per_xcd;
+    pp->n_tiles = n_out_per_head * shape->H / 256;  // at most 192 by 2^17 half tiles
     return RESS_OK;
 }
 

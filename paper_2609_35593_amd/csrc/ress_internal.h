@@ -62,7 +62,8 @@ struct ProjParams {
     int mode;
     int T, H;                 // tokens, heads (model width 64 H)
     int bq, bk, n_qb, n_kb;   // pooling grid (mode 0)
-    int m_tiles, n_tiles, items_per_xcd;
+    int n_tiles;              // output tiles of 256 columns
+    int m_full, m_half, full_per_xcd, half_per_xcd;  // row tiles, set by the launcher
     const uint16_t *a;        // mode 0: x [T][64H]; modes 1, 2: o [H][T][64]
     const uint16_t *w;        // [n_out][64H] (out features x in features)
     uint16_t *q, *k, *v;      // mode 0: bf16 [H][T][64]

@@ -10,9 +10,8 @@
 // sit in the B-operand layout of O^T = V^T P^T.
 //
 // Keys are consumed in 64-key chunks (one 64-key block of the kept list, or half
-// of a 128-key block). A chunk is two 32-key sub-tiles; for each, a wave issues
-// its 4 score MFMAs, forms the probabilities and issues its 4 PV MFMAs (the score
-// MFMAs of the second sub-tile go ahead of the PV MFMAs of the first). Latency is
+// of a 128-key block). A chunk is two 32-key sub-tiles; a wave issues
+// the 4 score MFMAs of each, forms the probabilities and issues the 8 PV MFMAs. Latency is
 // hidden by occupancy rather than by a software pipeline across chunks:
 // K and V chunks sit in two-slot rings of 8 KB per tensor and slot (32 KB per
 // workgroup), and the kernel fits 128 registers, so four 128-query workgroups
@@ -36,17 +35,21 @@
 //
 // Softmax: base-2 exponentials; row sums over the bf16-rounded probabilities
 // (the values the PV product consumes) with packed bf16 dot products. There is
-// no per-tile maximum: every row starts with reference 0 and forms its
-// probabilities against its reference; only when a sub-tile's sum exceeds 2^50,
-// or the row's running sum is still below 2^-100, is the sub-tile redone against
-// its true maximum (a result within +-40 of 0 is rounded to 0) and O rescaled.
-// While every row of a wave has reference 0, the wave runs a copy of the chunk
-// loop whose probabilities are exp2 of the score accumulators with nothing
-// else: Q is multiplied by scale*log2(e) when its fragments are loaded (one extra
-// bf16 rounding of Q), so the accumulators are base-2 logits. A wave whose first
-// 64 scores reach beyond +-24 in some row reloads Q unscaled instead, so large
-// logits are formed exactly; either way every score of a row has one form.
-// Softmax is invariant to the reference, so this changes rounding only.
+// no per-tile maximum: every row starts with reference 0. While every row of a wave
+// has reference 0, the wave runs a loop of its own whose probabilities are exp2 of the
+// score accumulators with nothing else: Q is multiplied by scale*log2(e) when its
+// fragments are loaded (one extra bf16 rounding of Q), so the accumulators are base-2
+// logits. It looks at a chunk's sum once, before the PV products: when it exceeds 2^50,
+// or the row's running sum is still below 2^-100, the wave goes over to the general
+// loop with that chunk. There every row forms its probabilities against its own
+// reference, and a sub-tile that leaves the same range is redone against its true
+// maximum (a result within +-40 of 0 is rounded to 0) and O rescaled. A wave whose first
+// 64 scores reach beyond +-24 in some row reloads Q unscaled and starts in the general
+// loop, so large logits are formed exactly; either way every score of a row has one
+// form. Softmax is invariant to the reference, so this changes rounding only.
+// (Measured, one loop over both forms with a look at every sub-tile -> two loops, one
+// look a chunk: the compiler kept two copies of O and moved all of it every other
+// chunk; 32 views, 75% sparsity 2,020 -> 1,885 us, dense 7,680 -> 7,165, 1,105 TFLOP/s.)
 //
 // Workgroups are numbered so that neighbouring query blocks of a head share an
 // XCD and its L2, where their K/V chunks are re-read, and heads of different cost
@@ -220,14 +223,12 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
         if constexpr (SPARSE) return e < n_ent ? klist[e] : -1;
         else return e < n_ent ? e : -1;
     };
-    auto valid = [&](int j) __attribute__((always_inline)) { return j >= 0 && j < n_kb; };
-    // First token of chunk ch of block j, and how many of its 64 keys are real.
+    // First token of chunk ch of block j, and how many of its 64 keys are real (none for
+    // an entry outside the layer).
     auto chunk_row0 = [&](int j, int ch) __attribute__((always_inline)) -> int {
-        return valid(j) ? j * BK + 64 * (ch & (CPE - 1)) : 0;
+        return j >= 0 && j < n_kb ? j * BK + 64 * (ch & (CPE - 1)) : N;
     };
-    auto chunk_keys = [&](int j, int ch) __attribute__((always_inline)) -> int {
-        return valid(j) ? max(0, min(64, N - j * BK - 64 * (ch & (CPE - 1)))) : 0;
-    };
+    auto chunk_keys = [&](int row0) __attribute__((always_inline)) -> int { return N - row0 < 64 ? N - row0 : 64; };
 
     // This head's K and V as buffer resources: N * 128 bytes (at most 2^31 for
     // N <= 2^24, as a 32-bit unsigned record count; row offsets stay below 2^31).
@@ -241,13 +242,23 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
     // every u: the swizzle depends on row bits 1-3 only).
     const int r0 = wave * 8 + (lane >> 3);
     const unsigned int coff = (unsigned int)(((lane & 7) ^ swz(r0)) << 4);
-    // Rows row0..row0+63 of one tensor into a slot; rows past N repeat row N-1.
-    auto dma_chunk = [&](__amdgpu_buffer_rsrc_t rs, int row0, unsigned char *dst) __attribute__((always_inline)) {
+    unsigned int doff[LPC];  // byte offsets of a full chunk's loads, against the chunk's first row
 #pragma unroll
-        for (int u = 0; u < LPC; ++u) {
-            const int row = min(row0 + r0 + 8 * NW * u, N - 1);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(dst + (u * NW + wave) * 1024), 16,
-                                                     (unsigned int)(row * 128) + coff, 0, 0, 0);
+    for (int u = 0; u < LPC; ++u) doff[u] = (unsigned int)((r0 + 8 * NW * u) * 128) + coff;
+    // Rows row0..row0+63 of one tensor into a slot; rows past N repeat row N-1 (the chunks
+    // that have any, and entries outside the layer, take the second form).
+    auto dma_chunk = [&](__amdgpu_buffer_rsrc_t rs, int row0, unsigned char *dst) __attribute__((always_inline)) {
+        if (row0 + 64 <= N) {
+#pragma unroll
+            for (int u = 0; u < LPC; ++u)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(dst + (u * NW + wave) * 1024), 16,
+                                                         (unsigned int)(doff[u] + 0u), row0 * 128, 0, 0);
+        } else {
+#pragma unroll
+            for (int u = 0; u < LPC; ++u) {
+                const unsigned int off = (unsigned int)(min(row0 + r0 + 8 * NW * u, N - 1) * 128) + coff;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(dst + (u * NW + wave) * 1024), 16, off, 0, 0, 0);
+            }
         }
     };
 
@@ -267,7 +278,6 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
         }
 
     float mref = 0.f;   // reference of this lane's query row (shared with lane^32), base-2 logits
-    bool zref = true;   // wave-uniform: every row has reference 0 (Q then is pre-scaled)
     float cw = 1.f;     // wave-uniform: base-2 logit per unit score (1 for pre-scaled Q, else c)
     float lrow = 0.f;
     f32x16 acc_o[2];
@@ -313,9 +323,8 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
         }
     };
     // Probabilities of a sub-tile, exp2(s) when every row has reference 0 (z), else
-    // exp2(s * cw - mref); returns the lane's sum of the bf16-rounded values.
-    auto probs = [&](auto z, const f32x16 &s, bf16x8 (&pb)[2]) __attribute__((always_inline)) -> float {
-        float l0 = 0.f, l1 = 0.f;
+    // exp2(s * cw - mref); l0 and l1 gather the lane's sum of the bf16-rounded values.
+    auto probs = [&](auto z, const f32x16 &s, bf16x8 (&pb)[2], float &l0, float &l1) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             float e[8];
@@ -332,18 +341,25 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
                 l1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pb[u][jj + 2], pb[u][jj + 3]}, ones, l1, false);
             }
         }
-        return l0 + l1;
     };
-    // Chunk-loop variants: every row's reference is 0 (zero), or per-row references (general).
     using general = std::integral_constant<bool, false>;
     using zero = std::integral_constant<bool, true>;
-    // Accept the sub-tile's probabilities, or redo them against a new reference
-    // (rescaling O and the running sum) when the sub-tile's sum exceeds kSumLimit,
-    // the row still has no mass above kTiny, or (zero variant) a row of the wave
-    // already left reference 0 in this chunk.
-    auto settle = [&](auto z, const f32x16 &s, bf16x8 (&pb)[2], float lh) __attribute__((always_inline)) {
-        constexpr bool Z = decltype(z)::value;
-        if (__any(!(lh <= kSumLimit) || lrow + lh < kTiny || (Z && mref != 0.f))) {
+    // One sub-tile against per-row references: accept its probabilities, or redo them
+    // against a new reference (rescaling O and the running sum) when their sum exceeds
+    // kSumLimit or the row still has no mass above kTiny.
+    auto general_tile = [&](const unsigned char *ks, const unsigned char *vs, int nv, int t)
+                            __attribute__((always_inline)) {
+        f32x16 s;
+        bf16x8 pb[2];
+        qk(ks, t, s);
+        if (nv < 64) {
+            asm volatile("" ::: "memory");
+            mask(s, nv, t);
+        }
+        float l0 = 0.f, l1 = 0.f;
+        probs(general{}, s, pb, l0, l1);
+        float lh = l0 + l1;
+        if (__any(!(lh <= kSumLimit) || lrow + lh < kTiny)) {
             float tmax = -INFINITY;
 #pragma unroll
             for (int v = 0; v < 16; ++v) tmax = fmaxf(tmax, s[v]);
@@ -371,62 +387,77 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc_o[dh][v] = (acc_o[dh][v] * alpha) * alpha;
             mref = mnew;
-            if (Z) zref = __all(mref == 0.f);
-            lh = probs(general{}, s, pb);
+            l0 = l1 = 0.f;
+            probs(general{}, s, pb, l0, l1);
+            lh = l0 + l1;
         }
         lrow += lh;
+        pv(vs, t, pb);
+    };
+    // A chunk of a wave whose rows all have reference 0: the probabilities of both
+    // sub-tiles are formed first and their sums looked at once. False (rare): the chunk
+    // leaves the range, and nothing of it has been taken.
+    // Partial chunks pay for the mask on a real branch (the empty asm keeps the
+    // compiler from if-converting it into every sub-tile).
+    auto zero_chunk = [&](const unsigned char *ks, const unsigned char *vs, int nv) __attribute__((always_inline)) {
+        bf16x8 p0[2], p1[2];
+        float l0 = 0.f, l1 = 0.f;
+        {
+            f32x16 s;
+            qk(ks, 0, s);
+            if (nv < 64) {
+                asm volatile("" ::: "memory");
+                mask(s, nv, 0);
+            }
+            probs(zero{}, s, p0, l0, l1);
+        }
+        {
+            f32x16 s;
+            qk(ks, 1, s);
+            if (nv < 64) {
+                asm volatile("" ::: "memory");
+                mask(s, nv, 1);
+            }
+            probs(zero{}, s, p1, l0, l1);
+        }
+        const float lh = l0 + l1;
+        if (__any(!(lh <= kSumLimit) || lrow + lh < kTiny)) return false;
+        lrow += lh;
+        pv(vs, 0, p0);
+        pv(vs, 1, p1);
+        return true;
     };
 
     int nv0 = 0, nv1 = 0;  // real keys of chunks ch and ch+1
     int jnext = -1;        // block of chunk ch+1, read one chunk ahead
-    // Chunk ch from slots (ks, vs); first the DMA of chunk ch+1 into (kd, vd), the
-    // slots of chunk ch-1 (free since the barrier that ended it).
-    auto iter = [&](auto z, int ch, const unsigned char *ks, const unsigned char *vs, unsigned char *kd,
-                    unsigned char *vd) __attribute__((always_inline)) {
+    // The DMA of chunk ch+1 into (kd, vd), the slots of chunk ch-1 (free since the
+    // barrier that ended it).
+    auto fetch = [&](int ch, unsigned char *kd, unsigned char *vd) __attribute__((always_inline)) {
         if (ch + 1 < C) {
-            const int j1 = jnext;
+            const int row1 = chunk_row0(jnext, ch + 1);
             jnext = ch + 2 < C ? block_of(ch + 2) : -1;
-            nv1 = __builtin_amdgcn_readfirstlane(chunk_keys(j1, ch + 1));
-            const int row1 = chunk_row0(j1, ch + 1);
+            nv1 = chunk_keys(row1);
             dma_chunk(krs, row1, kd);
             dma_chunk(vrs, row1, vd);
         }
-        // Sub-tile 0, then the score MFMAs of sub-tile 1 ahead of the PV MFMAs of
-        // sub-tile 0, so that the softmax of sub-tile 1 can start while those run.
-        // Partial chunks pay for the mask on a real branch (the empty asm keeps the
-        // compiler from if-converting it into every sub-tile).
-        f32x16 s0, s1;
-        bf16x8 p0[2], p1[2];
-        qk(ks, 0, s0);
-        if (nv0 < 64) {
-            asm volatile("" ::: "memory");
-            mask(s0, nv0, 0);
-        }
-        settle(z, s0, p0, probs(z, s0, p0));
-        qk(ks, 1, s1);
-        pv(vs, 0, p0);
-        if (nv0 < 64) {
-            asm volatile("" ::: "memory");
-            mask(s1, nv0, 1);
-        }
-        settle(z, s1, p1, probs(z, s1, p1));
-        pv(vs, 1, p1);
-        wait_vm_all();    // this wave's loads of chunk ch+1 have landed
-        __syncthreads();  // ... and every wave's; chunk ch's slots are no longer read
+    };
+    auto finish = [&]() __attribute__((always_inline)) {
+        wait_vm_all();    // this wave's loads of the next chunk have landed
+        __syncthreads();  // ... and every wave's; this chunk's slots are no longer read
         nv0 = nv1;
     };
 
     if (C > 0) {
         {
-            const int j0 = block_of(0);
-            nv0 = __builtin_amdgcn_readfirstlane(chunk_keys(j0, 0));
-            const int row0 = chunk_row0(j0, 0);
+            const int row0 = chunk_row0(block_of(0), 0);
+            nv0 = chunk_keys(row0);
             dma_chunk(krs, row0, k_s0);
             dma_chunk(vrs, row0, v_s0);
             jnext = C > 1 ? block_of(1) : -1;
         }
         wait_vm_all();
         __syncthreads();
+        bool zref;  // wave-uniform: every row has reference 0 (Q then is pre-scaled)
         {
             // Start with reference 0 only if every row's first 64 logits lie within
             // kStartBand; otherwise use unscaled Q (exact scores) from the start.
@@ -447,15 +478,36 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
             }
         }
         int ch = 0;
-        // A wave leaves the zero variant (for good) when a row's reference leaves 0;
-        // its Q stays pre-scaled (cw = 1), so every score of a row has one form.
-        for (;;) {
-            if (zref) iter(zero{}, ch, k_s0, v_s0, k_s1, v_s1);
-            else iter(general{}, ch, k_s0, v_s0, k_s1, v_s1);
-            if (++ch >= C) break;
-            if (zref) iter(zero{}, ch, k_s1, v_s1, k_s0, v_s0);
-            else iter(general{}, ch, k_s1, v_s1, k_s0, v_s0);
-            if (++ch >= C) break;
+        // Two loops, so that O keeps its registers in the first (one loop over both forms
+        // copied all 32 of them every other chunk). A wave leaves the zero form for good
+        // with the first chunk that does not fit it (that chunk's successor is on its way by
+        // then); its Q stays pre-scaled (cw = 1), so every score of a row has one form.
+        bool fetched = false;
+        if (zref)
+            for (;;) {
+                fetch(ch, k_s1, v_s1);
+                fetched = !zero_chunk(k_s0, v_s0, nv0);
+                if (fetched) break;
+                finish();
+                if (++ch >= C) break;
+                fetch(ch, k_s0, v_s0);
+                fetched = !zero_chunk(k_s1, v_s1, nv0);
+                if (fetched) break;
+                finish();
+                if (++ch >= C) break;
+            }
+        for (; ch < C; ++ch) {
+            if (ch & 1) {
+                if (!fetched) fetch(ch, k_s0, v_s0);
+                general_tile(k_s1, v_s1, nv0, 0);
+                general_tile(k_s1, v_s1, nv0, 1);
+            } else {
+                if (!fetched) fetch(ch, k_s1, v_s1);
+                general_tile(k_s0, v_s0, nv0, 0);
+                general_tile(k_s0, v_s0, nv0, 1);
+            }
+            fetched = false;
+            finish();
         }
     }
 

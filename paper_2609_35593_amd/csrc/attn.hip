@@ -117,21 +117,49 @@ __device__ __forceinline__ bool row_of(const AttnParams &p, bool sparse, int xcd
         return true;
     }
     const long long T = (long long)H * n, cap = p.seg_cap;
-    auto weight = [&](int hh) -> long long {
-        return sparse ? (long long)max(p.kept_count[(size_t)hh * n], 1) : 1ll;
-    };
-    long long W = 0;
-    for (int hh = 0; hh < H; ++hh) W += weight(hh) * n;
+    // Lane l holds the weights of heads l, l + 64, ... and their running sums (one load
+    // and one scan for all of them: head after head, each a dependent load, this took up
+    // to 10 us of every workgroup on the last XCDs).
+    constexpr int HC = RESS_MAX_HEADS / 64;
+    const int lane = threadIdx.x & 63;
+    int w[HC], sum[HC], total = 0;
+    if (sparse) {
+#pragma unroll
+        for (int c = 0; c < HC; ++c) {
+            w[c] = sum[c] = 0;
+            if (64 * c < H) {
+                const int hh = 64 * c + lane;
+                if (hh < H) w[c] = max(p.kept_count[(size_t)hh * n], 1);
+                int x = w[c];
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const int y = __shfl_up(x, o);
+                    x += lane >= o ? y : 0;
+                }
+                sum[c] = total + x;
+                total = __builtin_amdgcn_readlane(sum[c], 63);
+            }
+        }
+    } else {
+        total = H;
+    }
+    const long long W = (long long)total * n;
     // First row whose work prefix reaches x W / 8.
     auto split = [&](int x) -> long long {
         const long long target = (W / 8) * x + ((W % 8) * x + 7) / 8;
-        long long acc = 0;
-        for (int hh = 0; hh < H; ++hh) {
-            const long long w = weight(hh), seg = w * n;
-            if (acc + seg >= target)  // 0 < target - acc <= w n < 2^31
-                return (long long)hh * n + ((int)(target - acc) + (int)w - 1) / (int)w;
-            acc += seg;
-        }
+        if (!sparse) return target;
+#pragma unroll
+        for (int c = 0; c < HC; ++c)
+            if (64 * c < H) {
+                const unsigned long long at =
+                    __builtin_amdgcn_ballot_w64(64 * c + lane < H && (long long)sum[c] * n >= target);
+                if (at != 0ull) {
+                    const int l = __builtin_ctzll(at);
+                    const int wl = __builtin_amdgcn_readlane(w[c], l);
+                    const long long acc = (long long)(__builtin_amdgcn_readlane(sum[c], l) - wl) * n;
+                    return (long long)(64 * c + l) * n + ((int)(target - acc) + wl - 1) / wl;  // target - acc <= wl n < 2^31
+                }
+            }
         return T;
     };
     long long b = 0, e = 0;
@@ -149,26 +177,33 @@ __device__ __forceinline__ bool row_of(const AttnParams &p, bool sparse, int xcd
 
 // Four waves per SIMD for 128-query blocks (four 32 KB workgroups per CU); 64-query
 // blocks are held to two by the LDS (five 2-wave workgroups per CU).
-template <int BQ, int BK, bool SPARSE>
-__global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const AttnParams p)
+//
+// G > 1: G groups of BQ/32 waves share a query block, group g with its own slots taking
+// chunks g, g + G, ... of its list; the groups' O and sums are merged through the
+// slots at the end.
+template <int BQ, int BK, bool SPARSE, int G>
+__global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(const AttnParams p)
 {
-    constexpr int T = BQ * 2;                 // threads
-    constexpr int NW = BQ / 32;               // waves
+    constexpr int T = BQ * 2;                 // threads of a group
+    constexpr int NW = BQ / 32;               // waves of a group
     constexpr int CPE = BK / 64;              // 64-key chunks per kept-list entry
     constexpr int LPC = 64 * 8 / T;           // 16-byte DMA loads per thread, tensor and chunk
     constexpr int SLOT = 64 * 128;            // bytes of one chunk of K (or V)
     static_assert(64 * 8 % T == 0 && LPC >= 1, "a chunk must split evenly over the threads");
-    __shared__ __attribute__((aligned(1024))) unsigned char k_s0[SLOT];
-    __shared__ __attribute__((aligned(1024))) unsigned char k_s1[SLOT];
-    __shared__ __attribute__((aligned(1024))) unsigned char v_s0[SLOT];
-    __shared__ __attribute__((aligned(1024))) unsigned char v_s1[SLOT];
+    __shared__ __attribute__((aligned(1024))) unsigned char k_a0[G * SLOT];
+    __shared__ __attribute__((aligned(1024))) unsigned char k_a1[G * SLOT];
+    __shared__ __attribute__((aligned(1024))) unsigned char v_a0[G * SLOT];
+    __shared__ __attribute__((aligned(1024))) unsigned char v_a1[G * SLOT];
 
     const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
     int h, i;
     if (!row_of(p, SPARSE, xcd, local, h, i)) return;
     const int N = p.N, n_kb = p.n_kb;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_wg = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grp = G > 1 ? wave_wg / NW : 0, wave = wave_wg - grp * NW;  // key group, wave within it
+    unsigned char *const k_s0 = k_a0 + grp * SLOT, *const k_s1 = k_a1 + grp * SLOT;
+    unsigned char *const v_s0 = v_a0 + grp * SLOT, *const v_s1 = v_a1 + grp * SLOT;
     const int hh = lane >> 5, ql = lane & 31;
     const int g16 = (lane >> 4) & 1, s16 = lane & 15;
     const int q0 = i * BQ + wave * 32 + ql;
@@ -205,28 +240,30 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
     } else {
         n_ent = n_kb;
     }
-    int C = n_ent * CPE;  // 64-key chunks
+    int C_all = n_ent * CPE;  // 64-key chunks of the list
     if (CPE == 2 && n_ent > 0 && N - (n_kb - 1) * BK <= 64) {
         // The last block holds at most 64 tokens: its second chunk is empty.
         int jl;
         if constexpr (SPARSE) jl = list[n_ent - 1];
         else jl = n_ent - 1;
-        if (__builtin_amdgcn_readfirstlane(jl) == n_kb - 1) C -= 1;
+        if (__builtin_amdgcn_readfirstlane(jl) == n_kb - 1) C_all -= 1;
     }
+    // This group's chunks: chunk ch of the group is chunk grp + G ch of the list.
+    const int C = (C_all - grp + G - 1) / G;
 
     // Kept block indices through the scalar cache (wave-uniform addresses; the list
     // is read-only here).
     typedef const __attribute__((address_space(4))) int32_t cint32;
     const cint32 *klist = (const cint32 *)list;
     auto block_of = [&](int ch) __attribute__((always_inline)) -> int {
-        const int e = ch / CPE;
+        const int e = (grp + G * ch) / CPE;
         if constexpr (SPARSE) return e < n_ent ? klist[e] : -1;
         else return e < n_ent ? e : -1;
     };
     // First token of chunk ch of block j, and how many of its 64 keys are real (none for
     // an entry outside the layer).
     auto chunk_row0 = [&](int j, int ch) __attribute__((always_inline)) -> int {
-        return j >= 0 && j < n_kb ? j * BK + 64 * (ch & (CPE - 1)) : N;
+        return j >= 0 && j < n_kb ? j * BK + 64 * ((grp + G * ch) & (CPE - 1)) : N;
     };
     auto chunk_keys = [&](int row0) __attribute__((always_inline)) -> int { return N - row0 < 64 ? N - row0 : 64; };
 
@@ -359,7 +396,7 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
         float l0 = 0.f, l1 = 0.f;
         probs(general{}, s, pb, l0, l1);
         float lh = l0 + l1;
-        if (__any(!(lh <= kSumLimit) || lrow + lh < kTiny)) {
+        if (__builtin_amdgcn_ballot_w64(!(lh <= kSumLimit) || lrow + lh < kTiny) != 0ull) {
             float tmax = -INFINITY;
 #pragma unroll
             for (int v = 0; v < 16; ++v) tmax = fmaxf(tmax, s[v]);
@@ -396,11 +433,11 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
     };
     // A chunk of a wave whose rows all have reference 0: the probabilities of both
     // sub-tiles are formed first and their sums looked at once. False (rare): the chunk
-    // leaves the range, and nothing of it has been taken.
+    // leaves the range and is to be done against per-row references.
     // Partial chunks pay for the mask on a real branch (the empty asm keeps the
     // compiler from if-converting it into every sub-tile).
-    auto zero_chunk = [&](const unsigned char *ks, const unsigned char *vs, int nv) __attribute__((always_inline)) {
-        bf16x8 p0[2], p1[2];
+    auto zero_probs = [&](const unsigned char *ks, int nv, bf16x8 (&p0)[2], bf16x8 (&p1)[2], float &lh)
+                          __attribute__((always_inline)) -> bool {
         float l0 = 0.f, l1 = 0.f;
         {
             f32x16 s;
@@ -420,12 +457,8 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
             }
             probs(zero{}, s, p1, l0, l1);
         }
-        const float lh = l0 + l1;
-        if (__any(!(lh <= kSumLimit) || lrow + lh < kTiny)) return false;
-        lrow += lh;
-        pv(vs, 0, p0);
-        pv(vs, 1, p1);
-        return true;
+        lh = l0 + l1;
+        return __builtin_amdgcn_ballot_w64(!(lh <= kSumLimit) || lrow + lh < kTiny) == 0ull;
     };
 
     int nv0 = 0, nv1 = 0;  // real keys of chunks ch and ch+1
@@ -447,6 +480,7 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
         nv0 = nv1;
     };
 
+    if (G > 1 && C <= 0 && C_all > 0) __syncthreads();  // the others' first chunk
     if (C > 0) {
         {
             const int row0 = chunk_row0(block_of(0), 0);
@@ -483,19 +517,25 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
         // with the first chunk that does not fit it (that chunk's successor is on its way by
         // then); its Q stays pre-scaled (cw = 1), so every score of a row has one form.
         bool fetched = false;
-        if (zref)
-            for (;;) {
-                fetch(ch, k_s1, v_s1);
-                fetched = !zero_chunk(k_s0, v_s0, nv0);
-                if (fetched) break;
+        if (zref) {
+            auto zero_chunk = [&](const unsigned char *ks, const unsigned char *vs, unsigned char *kd, unsigned char *vd)
+                                  __attribute__((always_inline)) -> bool {
+                bf16x8 p0[2], p1[2];
+                float lh;
+                fetch(ch, kd, vd);
+                if (!zero_probs(ks, nv0, p0, p1, lh)) {
+                    fetched = true;
+                    return false;
+                }
+                lrow += lh;
+                pv(vs, 0, p0);
+                pv(vs, 1, p1);
                 finish();
-                if (++ch >= C) break;
-                fetch(ch, k_s0, v_s0);
-                fetched = !zero_chunk(k_s1, v_s1, nv0);
-                if (fetched) break;
-                finish();
-                if (++ch >= C) break;
+                return ++ch < C;
+            };
+            while (zero_chunk(k_s0, v_s0, k_s1, v_s1) && zero_chunk(k_s1, v_s1, k_s0, v_s0)) {
             }
+        }
         for (; ch < C; ++ch) {
             if (ch & 1) {
                 if (!fetched) fetch(ch, k_s0, v_s0);
@@ -511,8 +551,57 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
         }
     }
 
+    if constexpr (G > 1) {
+        // Groups with a chunk less wait at its barrier too.
+        for (int ch = max(C, 0); ch < (C_all + G - 1) / G; ++ch) __syncthreads();
+        // Every group but the first leaves its references, sums and O in LDS (the slots are
+        // free): 34 floats a lane, each a row of 64 lanes. The first rescales all of them
+        // to the largest reference among the groups that hold mass and adds them up in
+        // group order.
+        constexpr int PER = 34 * 64;  // floats per wave
+        constexpr int FIT = G * SLOT / (PER * 4);  // waves per slot array
+        static_assert((G - 1) * NW <= 4 * FIT, "merge area: the four slot arrays");
+        auto area = [&](int w) __attribute__((always_inline)) -> float * {
+            unsigned char *const a = w < FIT ? k_a0 : w < 2 * FIT ? v_a0 : w < 3 * FIT ? k_a1 : v_a1;
+            return reinterpret_cast<float *>(a) + w % FIT * PER;
+        };
+        lrow += __shfl_xor(lrow, 32);  // lanes l and l^32 share the row
+        if (grp > 0) {
+            float *m = area((grp - 1) * NW + wave) + lane;
+            m[0] = mref;
+            m[64] = lrow;
+#pragma unroll
+            for (int dh = 0; dh < 2; ++dh)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) m[(2 + dh * 16 + v) * 64] = acc_o[dh][v];
+        }
+        __syncthreads();
+        if (grp > 0) return;
+        float mtop = lrow > 0.f ? mref : -INFINITY;
+#pragma unroll
+        for (int g = 1; g < G; ++g) {
+            const float *m = area((g - 1) * NW + wave) + lane;
+            if (m[64] > 0.f) mtop = fmaxf(mtop, m[0]);
+        }
+        const float a0 = lrow > 0.f ? __builtin_amdgcn_exp2f(mref - mtop) : 0.f;
+        lrow *= a0;
+#pragma unroll
+        for (int dh = 0; dh < 2; ++dh)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc_o[dh][v] *= a0;
+#pragma unroll
+        for (int g = 1; g < G; ++g) {
+            const float *m = area((g - 1) * NW + wave) + lane;
+            const float a = m[64] > 0.f ? __builtin_amdgcn_exp2f(m[0] - mtop) : 0.f;
+            lrow = fmaf(m[64], a, lrow);
+#pragma unroll
+            for (int dh = 0; dh < 2; ++dh)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc_o[dh][v] = fmaf(m[(2 + dh * 16 + v) * 64], a, acc_o[dh][v]);
+        }
+    }
     // Each lane summed half of its row's keys; lanes l and l^32 share the row.
-    const float ltot = lrow + __shfl_xor(lrow, 32);
+    const float ltot = G > 1 ? lrow : lrow + __shfl_xor(lrow, 32);
     const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
     if (q0 < N && p.o32) {
         float *orow = p.o32 + (head + q0) * kD;
@@ -541,15 +630,32 @@ __global__ void __launch_bounds__(BQ * 2, BQ == 128 ? 4 : 2) attn_kernel(const A
     }
 }
 
+template <int BQ, int BK, int G>
+hipError_t launch_groups(const AttnParams &p, bool sparse, hipStream_t s)
+{
+    const dim3 grid((unsigned)(p.rotate ? 8 * p.H * p.seg_cap : 8 * p.seg_cap)), block(BQ * 2 * G);
+    if (sparse)
+        hipLaunchKernelGGL((attn_kernel<BQ, BK, true, G>), grid, block, 0, s, p);
+    else
+        hipLaunchKernelGGL((attn_kernel<BQ, BK, false, G>), grid, block, 0, s, p);
+    return hipGetLastError();
+}
+
+// Key groups per query block. One group where the rows fill the chip's 1,024 workgroup
+// places (four per CU at 128 queries) three times over; below that two, which halve
+// the time of a row and with it the last round and the rows that keep every block:
+// measured (us, one / two groups, 16 heads) 8 views 157 / 128 at 90% and 304 / 301 at
+// 50% sparsity, 16 views 434 / 309 at 90% and 540 / 543 at 75%, but 32 views 1,937 /
+// 2,071, where their shared barriers only cost. Four where even two leave most of the
+// chip idle (at most a workgroup per CU) and rows can be long enough to pay for the
+// merge: 4 heads of 4 views 69 / 54 / 47 with one / two / four.
 template <int BQ, int BK>
 hipError_t launch_bk(const AttnParams &p, bool sparse, hipStream_t s)
 {
-    const dim3 grid((unsigned)(p.rotate ? 8 * p.H * p.seg_cap : 8 * p.seg_cap)), block(BQ * 2);
-    if (sparse)
-        hipLaunchKernelGGL((attn_kernel<BQ, BK, true>), grid, block, 0, s, p);
-    else
-        hipLaunchKernelGGL((attn_kernel<BQ, BK, false>), grid, block, 0, s, p);
-    return hipGetLastError();
+    const long long rows = (long long)p.H * p.n_qb;
+    if (rows <= 256 && p.n_kb * (BK / 64) >= 64) return launch_groups<BQ, BK, 4>(p, sparse, s);
+    if (rows <= 3072) return launch_groups<BQ, BK, 2>(p, sparse, s);
+    return launch_groups<BQ, BK, 1>(p, sparse, s);
 }
 
 }  // namespace

@@ -1,0 +1,85 @@
+"""Attention with one, two and four key groups per query block against float64: lists
+of every length around the group count, ragged last chunks, entries outside the
+layer, rows whose mass sits in one group only, and logits that leave the range of the
+reference-0 form in one group and not in another."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def groups(H, n_qb, n_kb, bk):
+    """The library's rule, restated."""
+    rows = H * n_qb
+    return 4 if rows <= 256 and n_kb * (bk // 64) >= 64 else 2 if rows <= 3072 else 1
+
+
+def reference(q, k, v, count, idx, bq, bk, scale):
+    """softmax over the listed blocks' tokens (duplicates count twice), float64."""
+    import torch
+
+    H, N, _ = q.shape
+    out = torch.zeros(H, N, 64, dtype=torch.float64)
+    for h in range(H):
+        for i in range(count.shape[1]):
+            keys = [torch.arange(j * bk, min((j + 1) * bk, N)) for j in idx[h, i, :int(count[h, i])].tolist()
+                    if 0 <= j < idx.shape[2]]
+            if not keys:
+                continue
+            t = torch.cat(keys)
+            s = q[h, i * bq:(i + 1) * bq].double() @ k[h, t].double().T * scale
+            out[h, i * bq:(i + 1) * bq] = torch.softmax(s, 1) @ v[h, t].double()
+    return out
+
+
+CASES = [(1, 70 * 64 - 5, 64, 64, 4), (2, 33 * 128 + 1, 128, 128, 4), (2, 40 * 128 - 64, 128, 128, 4), (3, 700, 64, 64, 2),
+         (3, 1100, 128, 128, 2), (2, 1025, 64, 128, 2), (2, 900, 128, 64, 2), (70, 45 * 64 + 3, 64, 64, 1)]
+
+
+@pytest.mark.parametrize("spread", [1.0, 30.0])
+@pytest.mark.parametrize("H,N,bq,bk,G", CASES)
+def test_groups(H, N, bq, bk, G, spread):
+    import torch
+
+    import paper_2609_35593_amd as ress
+
+    n_qb, n_kb = -(-N // bq), -(-N // bk)
+    assert groups(H, n_qb, n_kb, bk) == G
+    rng = np.random.default_rng(H * 1000 + N)
+    gen = torch.Generator().manual_seed(N + int(spread))
+    q, k, v = (torch.randn(H, N, 64, generator=gen) for _ in range(3))
+    # Keys of every third block point along (or, spread > 1, far along and against) one direction of the queries,
+    # so that a row's mass and its logits' size differ from group to group.
+    d = torch.randn(64, generator=gen)
+    d /= d.norm()
+    q += 2.0 * d
+    for j in range(n_kb):
+        k[:, j * bk:(j + 1) * bk] += (spread if j % 3 == 0 else -spread if j % 3 == 1 else 0.0) * d
+    q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+    count = torch.zeros(H, n_qb, dtype=torch.int32)
+    idx = torch.full((H, n_qb, n_kb), -1, dtype=torch.int32)
+    for h in range(min(H, 3)):
+        for i in range(n_qb):
+            c = i % 8 if i < n_qb - 1 else n_kb  # empty rows, one block, ... and a full list
+            c = min(c, n_kb)
+            pick = np.sort(rng.choice(n_kb, c, replace=False)).astype(np.int32)
+            if c and i % 3 == 2:
+                pick[-1] = n_kb - 1  # the ragged last block
+            if c > 2 and i % 5 == 4:
+                pick[rng.integers(c)] = n_kb + 7  # contributes nothing
+            if c > 2 and i % 8 == 3:
+                pick[:] = np.where(np.arange(c) < c - 1, -1, pick)  # one entry that counts, after others that do not
+            count[h, i] = c
+            idx[h, i, :c] = torch.from_numpy(pick)
+    hs = min(H, 3)
+    got = ress.ress_sparse_attn_out_f32(q.cuda(), k.cuda(), v.cuda(), count.cuda(), idx.cuda(), bq=bq, bk=bk).cpu().double()
+    ref = reference(q[:hs], k[:hs], v[:hs], count[:hs], idx[:hs], bq, bk, 0.125)
+    assert torch.isfinite(got).all()
+    assert torch.all(got[hs:] == 0.0)
+    err = (got[:hs] - ref).abs()
+    # The probabilities are rounded to bf16 (2^-9 each, and their sum with them) and, in the reference-0 form, so is
+    # the scaled Q: 2^-9 of every product in a logit, at most 2^-9 L with L the largest sum of |q_d k_d| / 8. A weight
+    # that is off by a factor 1 + e moves the output by at most 2 e max|v|.
+    L = float((q[:hs].double().abs() @ k[:hs].double().abs().transpose(1, 2)).max()) * 0.125
+    bound = 2.0 * (2.0 ** -8 + 2.0 ** -9 * L) * float(v.double().abs().max())
+    assert float(err.max()) <= bound and float(err.mean()) <= 2e-3, (float(err.max()), bound, float(err.mean()))

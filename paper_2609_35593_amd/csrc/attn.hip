@@ -46,7 +46,7 @@
 // maximum (a result within +-40 of 0 is rounded to 0) and O rescaled. A wave whose first
 // 64 scores reach beyond +-24 in some row reloads Q unscaled and starts in the general
 // loop, so large logits are formed exactly; either way every score of a row has one
-// form. Softmax is invariant to the reference, so this changes rounding only.
+// form (all key groups of a row take their choice from the list's first 64 keys). Softmax is invariant to the reference, so this changes rounding only.
 // (Measured, one loop over both forms with a look at every sub-tile -> two loops, one
 // look a chunk: the compiler kept two copies of O and moved all of it every other
 // chunk; 32 views, 75% sparsity 2,020 -> 1,885 us, dense 7,680 -> 7,165, 1,105 TFLOP/s.)
@@ -496,12 +496,16 @@ __global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(con
         bool zref;  // wave-uniform: every row has reference 0 (Q then is pre-scaled)
         {
             // Start with reference 0 only if every row's first 64 logits lie within
-            // kStartBand; otherwise use unscaled Q (exact scores) from the start.
+            // kStartBand; otherwise use unscaled Q (exact scores) from the start. Every
+            // key group looks at the list's first chunk (group 0's slot, not refilled
+            // before the barrier that ends chunk 0): with a choice of their own, the groups
+            // could weigh one row's keys by pre-scaled and by exact scores, which differ by
+            // up to 2^-9 of the logit.
             float m0 = -INFINITY;
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 f32x16 s0;
-                qk(k_s0, t, s0);
+                qk(k_a0, t, s0);
 #pragma unroll
                 for (int v = 0; v < 16; ++v) m0 = fmaxf(m0, s0[v]);
             }

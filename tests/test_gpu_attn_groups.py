@@ -83,3 +83,24 @@ def test_groups(H, N, bq, bk, G, spread):
     L = float((q[:hs].double().abs() @ k[:hs].double().abs().transpose(1, 2)).max()) * 0.125
     bound = 2.0 * (2.0 ** -8 + 2.0 ** -9 * L) * float(v.double().abs().max())
     assert float(err.max()) <= bound and float(err.mean()) <= 2e-3, (float(err.max()), bound, float(err.mean()))
+
+
+@pytest.mark.parametrize("N,G", [(256, 2), (4096, 4)])
+def test_groups_share_one_form_of_the_scores(N, G):
+    """A row's first 64 keys choose between pre-scaled and exact scores for all of its groups: the other chunks' logits
+    are large, equal in two chunks of different groups and opposite in V, so the output is the difference of the two
+    groups' weights (0, but up to 0.1 where one group's scores are pre-scaled and the other's are not)."""
+    import torch
+
+    import paper_2609_35593_amd as ress
+
+    assert groups(1, N // 128, N // 64, 64) == G
+    q, k, v = (torch.zeros(1, N, 64) for _ in range(3))
+    q[0, :, 0] = torch.linspace(50.0, 60.0, N)  # base-2 logits of 90 to 108 against 10, about 1 against 0.1
+    k[0, :, 0] = 0.1
+    for chunk, sign in ((1, 1.0), (G, -1.0)):  # the second group's first chunk, the first group's second
+        k[0, 64 * chunk:64 * chunk + 64, 0] = 10.0
+        v[0, 64 * chunk:64 * chunk + 64] = sign
+    out = ress.ress_dense_attn(*(t.to(torch.bfloat16).cuda() for t in (q, k, v)), bq=128, bk=64).float().cpu()
+    # Equal scores, so equal weights: what is left is the rounding of the output and keys 2^-80 of the mass.
+    assert float(out.abs().max()) <= 2.0 ** -9, float(out.abs().max())

@@ -42,14 +42,21 @@
 // logits. It looks at a chunk's sum once, before the PV products: when it exceeds 2^50,
 // or the row's running sum is still below 2^-100, the wave goes over to the general
 // loop with that chunk. There every row forms its probabilities against its own
-// reference, and a sub-tile that leaves the same range is redone against its true
-// maximum (a result within +-40 of 0 is rounded to 0) and O rescaled. A wave whose first
-// 64 scores reach beyond +-24 in some row reloads Q unscaled and starts in the general
-// loop, so large logits are formed exactly; either way every score of a row has one
-// form (all key groups of a row take their choice from the list's first 64 keys). Softmax is invariant to the reference, so this changes rounding only.
+// reference, and a chunk that leaves the same range is formed again after the row's
+// reference has moved to 32 above its largest base-2 logit (O rescaled), which leaves
+// room on both sides. A wave whose first 64 scores reach beyond +-24 in some row
+// reloads Q unscaled and starts in the general loop, its references taken from those
+// scores, so large logits are formed exactly; either way every score of a row has one
+// form (all key groups of a row take their choice from the list's first 64 keys).
+// Softmax is invariant to the reference, so this changes rounding only.
 // (Measured, one loop over both forms with a look at every sub-tile -> two loops, one
 // look a chunk: the compiler kept two copies of O and moved all of it every other
-// chunk; 32 views, 75% sparsity 2,020 -> 1,885 us, dense 7,680 -> 7,165, 1,105 TFLOP/s.)
+// chunk; 32 views, 75% sparsity 2,020 -> 1,885 us, dense 7,680 -> 7,165, 1,105 TFLOP/s.
+// In the general loop, with Q 12 times as large, the one loop took 2,375 and 8,629 us at
+// 32 views and 652 and 2,212 at 16; a general loop that looked at each sub-tile and
+// rounded references within +-40 to 0 2,500 and 9,070, 779 and 2,488; this one 2,159 and
+// 8,172, 588 and 2,097. References 32 above the largest logit rather than at it save
+// 5-12% with Q 30 times as large.)
 //
 // Workgroups are numbered so that neighbouring query blocks of a head share an
 // XCD and its L2, where their K/V chunks are re-read, and heads of different cost
@@ -68,9 +75,9 @@ typedef float f32x16 __attribute__((__vector_size__(16 * sizeof(float))));
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-constexpr float kSumLimit = 0x1p50f;  // largest probability sum a sub-tile may reach
+constexpr float kSumLimit = 0x1p50f;  // largest probability sum a chunk may reach
 constexpr float kTiny = 0x1p-100f;    // a row whose running sum is below this has no usable reference
-constexpr float kZeroBand = 40.f;     // references within +-40 (base-2 logits) become 0
+constexpr float kHeadroom = 32.f;     // a new reference's distance above the row's largest logit so far
 constexpr float kStartBand = 24.f;    // first-chunk maxima a wave may have to start with reference 0
 
 __device__ __forceinline__ unsigned int bf16_bits(float x)
@@ -287,14 +294,17 @@ __global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(con
     auto dma_chunk = [&](__amdgpu_buffer_rsrc_t rs, int row0, unsigned char *dst) __attribute__((always_inline)) {
         if (row0 + 64 <= N) {
 #pragma unroll
-            for (int u = 0; u < LPC; ++u)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(dst + (u * NW + wave) * 1024), 16,
-                                                         (unsigned int)(doff[u] + 0u), row0 * 128, 0, 0);
+            for (int u = 0; u < LPC; ++u) {
+                const unsigned int off = doff[u];
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(dst + (u * NW + wave) * 1024), 16, off,
+                                                         row0 * 128, 0, 0);
+            }
         } else {
 #pragma unroll
             for (int u = 0; u < LPC; ++u) {
                 const unsigned int off = (unsigned int)(min(row0 + r0 + 8 * NW * u, N - 1) * 128) + coff;
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(dst + (u * NW + wave) * 1024), 16, off, 0, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(dst + (u * NW + wave) * 1024), 16, off, 0, 0,
+                                                         0);
             }
         }
     };
@@ -317,6 +327,7 @@ __global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(con
     float mref = 0.f;   // reference of this lane's query row (shared with lane^32), base-2 logits
     float cw = 1.f;     // wave-uniform: base-2 logit per unit score (1 for pre-scaled Q, else c)
     float lrow = 0.f;
+    float lpart = 0.f;  // lane^32's part of the row's sum, as of the last change of reference
     f32x16 acc_o[2];
 #pragma unroll
     for (int dh = 0; dh < 2; ++dh)
@@ -381,63 +392,51 @@ __global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(con
     };
     using general = std::integral_constant<bool, false>;
     using zero = std::integral_constant<bool, true>;
-    // One sub-tile against per-row references: accept its probabilities, or redo them
-    // against a new reference (rescaling O and the running sum) when their sum exceeds
-    // kSumLimit or the row still has no mass above kTiny.
-    auto general_tile = [&](const unsigned char *ks, const unsigned char *vs, int nv, int t)
-                            __attribute__((always_inline)) {
-        f32x16 s;
-        bf16x8 pb[2];
-        qk(ks, t, s);
-        if (nv < 64) {
-            asm volatile("" ::: "memory");
+    // New references for a chunk that leaves the range (its probabilities are then formed
+    // again): each row's true maximum over the chunk; O and the running sum rescaled.
+    auto rescale = [&](const unsigned char *ks, int nv) __attribute__((always_inline)) {
+        float tmax = -INFINITY;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            f32x16 s;
+            qk(ks, t, s);
             mask(s, nv, t);
-        }
-        float l0 = 0.f, l1 = 0.f;
-        probs(general{}, s, pb, l0, l1);
-        float lh = l0 + l1;
-        if (__builtin_amdgcn_ballot_w64(!(lh <= kSumLimit) || lrow + lh < kTiny) != 0ull) {
-            float tmax = -INFINITY;
 #pragma unroll
             for (int v = 0; v < 16; ++v) tmax = fmaxf(tmax, s[v]);
-            tmax = fmaxf(tmax, __shfl_xor(tmax, 32)) * cw;
-            // Decisions about the row's mass use the row's running sum: lanes l and
-            // l^32 each sum half of the row's keys (one of them may have no mass yet
-            // while the row has), and both must take the same reference.
-            const float lsum = lrow + __shfl_xor(lrow, 32);
-            // The reference only rises, except while the row has no usable mass yet:
-            // then it may fall to this sub-tile's maximum, but not below
-            // mref + log2(lsum), an upper bound of every earlier logit of the row, so
-            // that the rescaled running sums stay at most 1 (finite).
-            float mnew = fmaxf(mref, tmax);
-            // (log2 of a denormal sum may come back as -inf: -149 bounds it.)
-            if (lsum < kTiny) mnew = lsum > 0.f ? fmaxf(tmax, mref + fmaxf(__log2f(lsum), -149.f)) : tmax;
-            if (tmax == -INFINITY) mnew = mref;  // a fully masked sub-tile says nothing
-            if (fabsf(mnew) <= kZeroBand) mnew = 0.f;
-            // A row without mass has nothing to rescale (and 0 * exp2(large) must not
-            // happen); otherwise the factor is applied as two halves, each finite
-            // for shifts up to 2^8 (a running sum as small as the smallest denormal).
-            const float alpha = lsum > 0.f ? __builtin_amdgcn_exp2f(0.5f * (mref - mnew)) : 0.f;
-            lrow = (lrow * alpha) * alpha;
-#pragma unroll
-            for (int dh = 0; dh < 2; ++dh)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc_o[dh][v] = (acc_o[dh][v] * alpha) * alpha;
-            mref = mnew;
-            l0 = l1 = 0.f;
-            probs(general{}, s, pb, l0, l1);
-            lh = l0 + l1;
         }
-        lrow += lh;
-        pv(vs, t, pb);
+        tmax = fmaxf(tmax, __shfl_xor(tmax, 32)) * cw + kHeadroom;
+        // Decisions about the row's mass use the row's running sum: lanes l and
+        // l^32 each sum half of the row's keys (one of them may have no mass yet
+        // while the row has), and both must take the same reference.
+        lpart = __shfl_xor(lrow, 32);
+        const float lsum = lrow + lpart;
+        // The reference only rises, except while the row has no usable mass yet:
+        // then it may fall to this chunk's maximum, but not below
+        // mref + log2(lsum), an upper bound of every earlier logit of the row, so
+        // that the rescaled running sums stay at most 1 (finite).
+        float mnew = fmaxf(mref, tmax);
+        // (log2 of a denormal sum may come back as -inf: -149 bounds it.)
+        if (lsum < kTiny) mnew = lsum > 0.f ? fmaxf(tmax, mref + fmaxf(__log2f(lsum), -149.f)) : tmax;
+        if (tmax == -INFINITY) mnew = mref;  // a fully masked chunk says nothing
+        // A row without mass has nothing to rescale (and 0 * exp2(large) must not
+        // happen); otherwise the factor is applied as two halves, each finite
+        // for shifts up to 2^8 (a running sum as small as the smallest denormal).
+        const float alpha = lsum > 0.f ? __builtin_amdgcn_exp2f(0.5f * (mref - mnew)) : 0.f;
+        lrow = (lrow * alpha) * alpha;
+        lpart = (lpart * alpha) * alpha;
+#pragma unroll
+        for (int dh = 0; dh < 2; ++dh)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc_o[dh][v] = (acc_o[dh][v] * alpha) * alpha;
+        mref = mnew;
     };
-    // A chunk of a wave whose rows all have reference 0: the probabilities of both
-    // sub-tiles are formed first and their sums looked at once. False (rare): the chunk
-    // leaves the range and is to be done against per-row references.
+    // A chunk against the rows' present references (all 0 in the zero form): the
+    // probabilities of both sub-tiles are formed first and their sums looked at once.
+    // False (rare): the chunk leaves the range.
     // Partial chunks pay for the mask on a real branch (the empty asm keeps the
     // compiler from if-converting it into every sub-tile).
-    auto zero_probs = [&](const unsigned char *ks, int nv, bf16x8 (&p0)[2], bf16x8 (&p1)[2], float &lh)
-                          __attribute__((always_inline)) -> bool {
+    auto chunk_probs = [&](auto z, const unsigned char *ks, int nv, bf16x8 (&p0)[2], bf16x8 (&p1)[2], float have,
+                           float &lh) __attribute__((always_inline)) -> bool {
         // (The compiler's MFMA/LDS interleaving: 2% with key groups, -1% without.)
         if constexpr (G > 1) __builtin_amdgcn_iglp_opt(0);
         float l0 = 0.f, l1 = 0.f;
@@ -448,7 +447,7 @@ __global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(con
                 asm volatile("" ::: "memory");
                 mask(s, nv, 0);
             }
-            probs(zero{}, s, p0, l0, l1);
+            probs(z, s, p0, l0, l1);
         }
         {
             f32x16 s;
@@ -457,10 +456,10 @@ __global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(con
                 asm volatile("" ::: "memory");
                 mask(s, nv, 1);
             }
-            probs(zero{}, s, p1, l0, l1);
+            probs(z, s, p1, l0, l1);
         }
         lh = l0 + l1;
-        return __builtin_amdgcn_ballot_w64(!(lh <= kSumLimit) || lrow + lh < kTiny) == 0ull;
+        return __builtin_amdgcn_ballot_w64(!(lh <= kSumLimit) || have + lh < kTiny) == 0ull;
     };
 
     int nv0 = 0, nv1 = 0;  // real keys of chunks ch and ch+1
@@ -500,7 +499,7 @@ __global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(con
             // key group looks at the list's first chunk (group 0's slot, not refilled
             // before the barrier that ends chunk 0): with a choice of their own, the groups
             // could weigh one row's keys by pre-scaled and by exact scores, which differ by
-            // up to 2^-9 of the logit.
+            // up to 2^-8 of the logit.
             float m0 = -INFINITY;
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
@@ -514,11 +513,12 @@ __global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(con
             if (!zref) {
                 load_q(false);
                 cw = c;
+                if (fabsf(m0) < INFINITY) mref = m0 + kHeadroom;
                 wait_vm_all();  // Q lands here, not at the first MFMA of every chunk
             }
         }
         int ch = 0;
-        // Two loops, so that O keeps its registers in the first (one loop over both forms
+        // Two loops, so that O keeps its registers in each (one loop over both forms
         // copied all 32 of them every other chunk). A wave leaves the zero form for good
         // with the first chunk that does not fit it (that chunk's successor is on its way by
         // then); its Q stays pre-scaled (cw = 1), so every score of a row has one form.
@@ -529,7 +529,7 @@ __global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(con
                 bf16x8 p0[2], p1[2];
                 float lh;
                 fetch(ch, kd, vd);
-                if (!zero_probs(ks, nv0, p0, p1, lh)) {
+                if (!chunk_probs(zero{}, ks, nv0, p0, p1, lrow, lh)) {
                     fetched = true;
                     return false;
                 }
@@ -543,18 +543,29 @@ __global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(con
             while (zero_chunk(k_s0, v_s0, k_s1, v_s1) && zero_chunk(k_s1, v_s1, k_s0, v_s0)) {
             }
         }
-        for (; ch < C; ++ch) {
-            if (ch & 1) {
-                if (!fetched) fetch(ch, k_s0, v_s0);
-                general_tile(k_s1, v_s1, nv0, 0);
-                general_tile(k_s1, v_s1, nv0, 1);
-            } else {
-                if (!fetched) fetch(ch, k_s1, v_s1);
-                general_tile(k_s0, v_s0, nv0, 0);
-                general_tile(k_s0, v_s0, nv0, 1);
-            }
+        auto general_chunk = [&](const unsigned char *ks, const unsigned char *vs, unsigned char *kd,
+                                 unsigned char *vd) __attribute__((always_inline)) -> bool {
+            bf16x8 p0[2], p1[2];
+            float lh;
+            if (!fetched) fetch(ch, kd, vd);
             fetched = false;
+            if (!chunk_probs(general{}, ks, nv0, p0, p1, lrow + lpart, lh)) {
+                rescale(ks, nv0);
+                chunk_probs(general{}, ks, nv0, p0, p1, lrow + lpart, lh);
+            }
+            if constexpr (G > 1) __builtin_amdgcn_iglp_opt(0);
+            lrow += lh;
+            pv(vs, 0, p0);
+            pv(vs, 1, p1);
             finish();
+            return ++ch < C;
+        };
+        // (A copy of the chunk for each slot: slot addresses formed at run time cost 2-8%.
+        // Of the ways to enter at either slot, this one leaves O in its registers.)
+        bool odd = ch & 1;
+        while (ch < C) {
+            if (odd || general_chunk(k_s0, v_s0, k_s1, v_s1)) general_chunk(k_s1, v_s1, k_s0, v_s0);
+            odd = false;
         }
     }
 

@@ -1,7 +1,7 @@
 """Attention with one, two and four key groups per query block against float64: lists
 of every length around the group count, ragged last chunks, entries outside the
-layer, rows whose mass sits in one group only, and logits that leave the range of the
-reference-0 form in one group and not in another."""
+layer, and rows whose mass sits in one group only. (Rows that leave the reference-0 form:
+test_gpu_attn_references.)"""
 import numpy as np
 import pytest
 
@@ -49,7 +49,7 @@ def test_groups(H, N, bq, bk, G, spread):
     gen = torch.Generator().manual_seed(N + int(spread))
     q, k, v = (torch.randn(H, N, 64, generator=gen) for _ in range(3))
     # Keys of every third block point along (or, spread > 1, far along and against) one direction of the queries,
-    # so that a row's mass and its logits' size differ from group to group.
+    # so that a row's mass differs from group to group.
     d = torch.randn(64, generator=gen)
     d /= d.norm()
     q += 2.0 * d

@@ -136,7 +136,7 @@ __device__ __forceinline__ bool row_of(const AttnParams &p, bool sparse, int xcd
             w[c] = sum[c] = 0;
             if (64 * c < H) {
                 const int hh = 64 * c + lane;
-                if (hh < H) w[c] = max(p.kept_count[(size_t)hh * n], 1);
+                if (hh < H) w[c] = min(max(p.kept_count[(size_t)hh * n], 1), p.n_kb);  // sums fit 31 bits
                 int x = w[c];
 #pragma unroll
                 for (int o = 1; o < 64; o <<= 1) {
@@ -164,7 +164,8 @@ __device__ __forceinline__ bool row_of(const AttnParams &p, bool sparse, int xcd
                     const int l = __builtin_ctzll(at);
                     const int wl = __builtin_amdgcn_readlane(w[c], l);
                     const long long acc = (long long)(__builtin_amdgcn_readlane(sum[c], l) - wl) * n;
-                    return (long long)(64 * c + l) * n + ((int)(target - acc) + wl - 1) / wl;  // target - acc <= wl n < 2^31
+                    // target - acc <= wl n < 2^31
+                    return (long long)(64 * c + l) * n + ((int)(target - acc) + wl - 1) / wl;
                 }
             }
         return T;

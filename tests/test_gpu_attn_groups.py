@@ -104,3 +104,23 @@ def test_groups_share_one_form_of_the_scores(N, G):
     out = ress.ress_dense_attn(*(t.to(torch.bfloat16).cuda() for t in (q, k, v)), bq=128, bk=64).float().cpu()
     # Equal scores, so equal weights: what is left is the rounding of the output and keys 2^-80 of the mass.
     assert float(out.abs().max()) <= 2.0 ** -9, float(out.abs().max())
+
+
+@pytest.mark.parametrize("H,N", [(12, 1500), (256, 300)])
+def test_counts_beyond_the_layer(H, N):
+    """Counts outside [0, n_kb] are clamped wherever they are read: by the rows and by the order of the work, which
+    adds them up over the heads."""
+    import torch
+
+    import paper_2609_35593_amd as ress
+
+    gen = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn(H, N, 64, generator=gen, device="cuda").to(torch.bfloat16) for _ in range(3))
+    n_qb, n_kb = -(-N // 128), -(-N // 64)
+    idx = torch.arange(n_kb, dtype=torch.int32, device="cuda").expand(H, n_qb, n_kb).contiguous()
+    raw = torch.full((H, n_qb), 2 ** 31 - 1, dtype=torch.int32, device="cuda")
+    raw[1::3] = 3
+    raw[2::5] = -2 ** 31
+    out = [ress.ress_sparse_attn(q, k, v, c, idx, bq=128, bk=64) for c in (raw, raw.clamp(0, n_kb))]
+    assert torch.equal(*out)
+    assert torch.equal(out[0][0], ress.ress_dense_attn(q, k, v, bq=128, bk=64)[0])

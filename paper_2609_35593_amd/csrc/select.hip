@@ -872,7 +872,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) select_kernel(const SelectPar
                     slot_fence(c);
                 }
             };
-            if (eps >= 1e-100)
+            if (eps >= 1e-100 && eps <= 1e100)  // the divisor, at least eps^2, is far from the range's ends
                 gains([](double x, double d) { return quot(x, d); });
             else
                 gains([](double x, double d) { return x / d; });

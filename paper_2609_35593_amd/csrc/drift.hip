@@ -19,8 +19,8 @@
 //    into one (M + M^T, exact or once rounded in float64), so 10 of the 16 blocks
 //    are multiplied. Their A operands, 40 float64 values a lane, are read once per
 //    wave and stay in registers.
-// Roofline: 1.25 GFLOP of float64 matrix steps and 90 MB (two float32 inputs) at 16
-// heads x 10,992 tokens, 14 and 18 us at 78.6 TFLOP/s and 5.1 TB/s. Measured there:
+// Roofline: 0.90 GFLOP of float64 matrix steps (40 a tile) and 90 MB (two float32 inputs)
+// at 16 heads x 10,992 tokens, 11.5 and 18 us at 78.6 TFLOP/s and 5.1 TB/s. Measured there:
 // 30 us (one lane per channel with M and x read from LDS for every token: 145 us).
 #include "ress_internal.h"
 
@@ -50,7 +50,7 @@ __global__ void __launch_bounds__(kThreads, 2) drift_sq_kernel(const DriftSqPara
     const float *Mh = p.gram + (size_t)h * kD * kD;
 
     // The two inputs' 16 channels of this lane's token (rows past the block repeat its
-    // last row; their x is zeroed).
+    // last row and are left out of the sum).
     auto load = [&](int t, float4 (&xa)[4], float4 (&xb)[4]) __attribute__((always_inline)) {
         const size_t off = ((size_t)h * p.N + min(t + col, t1 - 1)) * kD + 4 * g;
 #pragma unroll
@@ -82,14 +82,14 @@ __global__ void __launch_bounds__(kThreads, 2) drift_sq_kernel(const DriftSqPara
     double acc = 0.0;
     for (; t < t1; t += 16 * kWaves) {
         double x[4][4];
-        const bool in = t + col < t1;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            x[u][0] = in ? (double)xa[u].x - (double)xb[u].x : 0.0;
-            x[u][1] = in ? (double)xa[u].y - (double)xb[u].y : 0.0;
-            x[u][2] = in ? (double)xa[u].z - (double)xb[u].z : 0.0;
-            x[u][3] = in ? (double)xa[u].w - (double)xb[u].w : 0.0;
+            x[u][0] = (double)xa[u].x - (double)xb[u].x;
+            x[u][1] = (double)xa[u].y - (double)xb[u].y;
+            x[u][2] = (double)xa[u].z - (double)xb[u].z;
+            x[u][3] = (double)xa[u].w - (double)xb[u].w;
         }
+        const bool in = t + col < t1;
         if (t + 16 * kWaves < t1) load(t + 16 * kWaves, xa, xb);
         v4d c[4];
 #pragma unroll
@@ -102,10 +102,13 @@ __global__ void __launch_bounds__(kThreads, 2) drift_sq_kernel(const DriftSqPara
 #pragma unroll
                 for (int nt = 0; nt <= u; ++nt)
                     c[nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(m[nt][u][e], x[u][e], c[nt], 0, 0, 0);
+        // (A zero x would not do for the rows past the block: M need not be finite.)
+        double with = acc;
 #pragma unroll
         for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) acc = fma(x[nt][v], c[nt][v], acc);
+            for (int v = 0; v < 4; ++v) with = fma(x[nt][v], c[nt][v], with);
+        acc = in ? with : acc;
     }
     acc = wave_sum(acc);
     if (lane == 0) part[wave] = acc;

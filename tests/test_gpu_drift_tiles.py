@@ -29,3 +29,19 @@ def test_drift_tile_edges(N, bq):
         ref = np.einsum("htc,hcd,htd->h", xs, gram.astype(np.float64), xs)
         mag = np.einsum("htc,hcd,htd->h", np.abs(xs), np.abs(gram).astype(np.float64), np.abs(xs))
         assert np.all(np.abs(got[:, i] - ref) <= 2.0 ** -40 * mag)
+
+
+@pytest.mark.parametrize("N", [16, 17, 70, 128, 130])
+def test_drift_infinite_gram(N):
+    """A Gram matrix with an infinite diagonal entry gives an infinite result in every block, ragged ones too: the
+    rows that pad a block's last tile have no part in it."""
+    import torch
+
+    import paper_2609_35593_amd as ress
+
+    rng = np.random.default_rng(N)
+    a, b = (torch.from_numpy(rng.standard_normal((1, N, 64)).astype(np.float32)).cuda() for _ in range(2))
+    gram = torch.from_numpy(rng.standard_normal((1, 64, 64)).astype(np.float32)).cuda()
+    gram[0, 5, 5] = float("inf")
+    got = ress.ress_block_drift_sq(a, b, gram, bq=128)
+    assert bool((got == float("inf")).all()), got

@@ -315,10 +315,10 @@ __device__ __forceinline__ typename slot_bits<(CPL > 32)>::type topk_slots(const
 }
 
 // Sizes of a workgroup configuration: NW waves of R rows each, RW = NW R rows in MT
-// 16-row tiles. LDS holds, per row, one staging row of SW slots (64 key blocks
-// each, padded by 16 bytes so that rows start on different banks) and two vectors
-// of 64 channels (padded likewise), and M_h where it fits beside them.
-template <int CPL, int R, int NW>
+// 16-row tiles; WPC workgroups share a CU. LDS holds, per row, one staging row of SW
+// slots (64 key blocks each, padded by 16 bytes so that rows start on different banks)
+// and two vectors of 64 channels (padded likewise), and M_h where it fits beside them.
+template <int CPL, int R, int NW, int WPC>
 struct SelCfg {
     static constexpr int RW = NW * R;
     static constexpr int MT = (RW + 15) / 16;
@@ -329,24 +329,24 @@ struct SelCfg {
     static constexpr int SROW = SW * 64 + 2;  // doubles per staging row
     static constexpr int VROW = kD + 2;       // doubles per vector
     static constexpr int BYTES = RW * (SROW + 2 * VROW) * 8;
-    static constexpr bool M_LDS = BYTES + kD * (kD + 1) * 4 + 64 <= 163840;
+    static constexpr bool M_LDS = WPC * (BYTES + kD * (kD + 1) * 4 + 64) <= 163840;
     static constexpr int TPW = (4 * CPL + NW - 1) / NW;  // key-block tiles per wave, at most
     // Tiles of Vbar a wave keeps in registers for all its passes (32 registers
     // each), as far as they fit beside the rows' state.
-    static constexpr int REGS = 2048 / NW;  // registers per lane: one workgroup per CU
+    static constexpr int REGS = 2048 / (NW * WPC);  // registers per lane
     static constexpr int STATE = 4 * R * CPL + CPL + 60 + 25 * R;
     static constexpr int VT = STATE + 32 * TPW <= REGS ? TPW : (STATE + 32 <= REGS ? 1 : 0);
     static constexpr int FENCE = REGS - 4 * R * CPL - 32 * VT >= 128 ? 0 : (REGS - 4 * R * CPL - 32 * VT >= 90 ? 2 : 1);
     using bits = typename slot_bits<(CPL > 32)>::type;
-    static_assert(BYTES <= 163840, "LDS of one CU");
+    static_assert(WPC * BYTES <= 163840, "LDS of one CU");
     static_assert(KS >= 1, "one weighted-sum item per wave at most");
     static_assert(4 * MT <= NW, "one mat-vec item per wave at most");
 };
 
-template <int CPL, int R, int NW>
-__global__ void __launch_bounds__(NW * 64, NW / 4) select_kernel(const SelectParams p)
+template <int CPL, int R, int NW, int WPC>
+__global__ void __launch_bounds__(NW * 64, NW * WPC / 4) select_kernel(const SelectParams p)
 {
-    using Cfg = SelCfg<CPL, R, NW>;
+    using Cfg = SelCfg<CPL, R, NW, WPC>;
     constexpr int RW = Cfg::RW, MT = Cfg::MT, SROW = Cfg::SROW, VROW = Cfg::VROW, KS = Cfg::KS, VT = Cfg::VT;
     constexpr int TPW = Cfg::TPW;
     constexpr bool M_LDS = Cfg::M_LDS;
@@ -961,13 +961,13 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) select_kernel(const SelectPar
     }
 }
 
-template <int CPL, int R, int NW>
+template <int CPL, int R, int NW, int WPC = 1>
 hipError_t launch_cfg(const SelectParams &p, hipStream_t s)
 {
     SelectParams q = p;
     const int groups = (p.n_qb + NW * R - 1) / (NW * R);
     q.items_per_xcd = (p.H * groups + 7) / 8;
-    hipLaunchKernelGGL((select_kernel<CPL, R, NW>), dim3((unsigned)(8 * q.items_per_xcd)), dim3(NW * 64), 0, s, q);
+    hipLaunchKernelGGL((select_kernel<CPL, R, NW, WPC>), dim3((unsigned)(8 * q.items_per_xcd)), dim3(NW * 64), 0, s, q);
     return hipGetLastError();
 }
 
@@ -977,27 +977,37 @@ hipError_t launch_cfg(const SelectParams &p, hipStream_t s)
 // over 8, 16, 32 and 100 views (us with 4 / 8 / 12 / 16 / 24 rows): 67 / 73 / 85 / 90 /
 // 158 at 344 key blocks, - / 129 / 140 / 158 at 687, - / 176 / 193 / 231 at 1,074; more
 // waves hide each other's latencies until they share the vector unit, more rows per
-// wave only add up. In hundredths of 8 rows: 90, 100, 112, 127, 210.
+// wave only add up. In hundredths of 8 rows: 90, 100, 112, 127, 210. (Every shape tried
+// at 21 key-block counts from 3 to 1,074 and 4 to 256 heads: the rule takes the fastest
+// or one within 2% of it.)
+// Up to 2 slots there is also 8 waves of two, two workgroups a CU, 215 for two at once
+// and 135 for a CU's odd last one: layers of many heads and few key blocks fill the chip
+// several times over, where full 16-row tiles and two workgroups in turn count for more
+// than a row's latency. At 100 key blocks, 64 / 128 / 256 heads: 154 / 295 / 549 us
+// without it, 139 / 264 / 486 with it; 128 key blocks 175 / 339 / 677 and 160 / 307 / 604.
 constexpr long long kCUs = 256;
 template <int CPL>
 hipError_t launch_rows(const SelectParams &p, hipStream_t s)
 {
-    auto cost = [&](int rows, int weight) {
+    auto rounds = [&](int rows) {
         const long long wg = (long long)p.H * ((p.n_qb + rows - 1) / rows);
-        return ((wg + kCUs - 1) / kCUs) * weight;
+        return (wg + kCUs - 1) / kCUs;
     };
     int best = 8;
-    long long bc = cost(8, 100);
+    long long bc = rounds(8) * 100;
     auto consider = [&](int rows, int weight) {
-        if (cost(rows, weight) < bc) best = rows, bc = cost(rows, weight);
+        if (rounds(rows) * weight < bc) best = rows, bc = rounds(rows) * weight;
     };
     consider(4, 90);
     consider(12, 112);
     consider(16, 127);
-    if constexpr (CPL <= 6) {
-        consider(24, 210);
-        if (best == 24) return launch_cfg<CPL, 2, 12>(p, s);
+    if constexpr (CPL <= 6) consider(24, 210);
+    if constexpr (CPL <= 2) {
+        const long long each = rounds(16);
+        if (each / 2 * 215 + each % 2 * 135 < bc) return launch_cfg<CPL, 2, 8, 2>(p, s);
     }
+    if constexpr (CPL <= 6)
+        if (best == 24) return launch_cfg<CPL, 2, 12>(p, s);
     if (best == 16) return launch_cfg<CPL, 1, 16>(p, s);
     if (best == 12) return launch_cfg<CPL, 1, 12>(p, s);
     if (best == 8) return launch_cfg<CPL, 1, 8>(p, s);

@@ -8,27 +8,14 @@ import pytest
 import oracle
 import synth
 from gpu_helpers import compare_select, gpu_select, say
+from launch_rules import select_shape
 
 pytestmark = pytest.mark.gpu
 
 
-def launch_shape(H, n_qb, n_kb):
-    """The library's launch rule, restated."""
-    for lim, cpl in ((128, 2), (256, 4), (384, 6), (512, 8), (768, 12), (1088, 17), (1536, 24), (2304, 36), (4096, 64)):
-        if n_kb <= lim:
-            break
-    if cpl > 17:
-        return cpl, 4 if cpl == 64 else 8
-    best = None
-    for rows, weight in ((8, 100), (4, 90), (12, 112), (16, 127)) + (((24, 210),) if cpl <= 6 else ()):
-        cost = -(-(H * -(-n_qb // rows)) // 256) * weight
-        if best is None or cost < best[0]:
-            best = (cost, rows)
-    return cpl, best[1]
-
-
-# (key blocks of 64 tokens, heads, slots per lane, rows per workgroup)
-SHAPES = [(120, 1, 2, 4), (120, 9, 2, 8), (120, 18, 2, 12), (120, 26, 2, 16), (120, 35, 2, 24),
+# (key blocks of 64 tokens, heads, slots per lane, rows per workgroup; 216: two workgroups of 8 waves of two)
+SHAPES = [(120, 1, 2, 4), (120, 9, 2, 8), (120, 18, 2, 12), (120, 26, 2, 16), (120, 35, 2, 24), (120, 52, 2, 216),
+          (120, 80, 2, 216),
           (200, 1, 4, 4), (200, 6, 4, 8), (200, 11, 4, 12), (200, 16, 4, 16), (200, 21, 4, 24),
           (350, 1, 6, 4), (350, 3, 6, 8), (350, 6, 6, 12), (350, 9, 6, 16), (350, 12, 6, 24),
           (450, 1, 8, 4), (450, 3, 8, 8), (450, 5, 8, 12), (450, 7, 8, 16),
@@ -40,7 +27,8 @@ SHAPES = [(120, 1, 2, 4), (120, 9, 2, 8), (120, 18, 2, 12), (120, 26, 2, 16), (1
 @pytest.mark.parametrize("n_kb,H,cpl,rows", SHAPES)
 def test_launch_shapes(n_kb, H, cpl, rows):
     L = synth.make_layer(8, n_kb * 8 - 5, 5, H=H, block=64, sparsity=0.55, seed=70 + cpl * 4 + rows, name=f"{n_kb} blocks H={H}")
-    assert L.n_kb == n_kb and launch_shape(L.H, L.n_qb, L.n_kb) == (cpl, rows)
+    waves, per_wave = {24: (12, 2), 216: (8, 2)}.get(rows, (rows, 1))
+    assert L.n_kb == n_kb and select_shape(L.H, L.n_qb, L.n_kb) == (cpl, (waves, per_wave))
     say(f"[select shape] slots {cpl}, rows {rows}: H={L.H} N={L.N} n_kb={L.n_kb}")
     rng = np.random.default_rng(cpl * 10 + rows)
     pick = np.unique(np.concatenate([rng.integers(0, L.H * L.n_qb, 60), [0, L.n_qb - 1, L.H * L.n_qb - 1]]))

@@ -9,6 +9,7 @@ import pytest
 import synth
 from gpu_helpers import (compare_attn, compare_attn_values, compare_select, device_inputs, gpu_select,
                          oracle_select, sample_tokens, say, stack_layer)
+from launch_rules import select_shape
 
 pytestmark = pytest.mark.gpu
 
@@ -293,8 +294,8 @@ def test_config_32v_q128_k64(ress):
 
 
 def test_select_one_row_per_wave_range(ress):
-    """385-768 key blocks run one row per wave (8 slots per lane here): 22 views on
-    the 128/64 grid, 473 key blocks, every row."""
+    """From 385 key blocks on every wave has one row (8 slots per lane here): 22 views
+    on the 128/64 grid, 473 key blocks, every row."""
     L = synth.make_layer(22, 1369, 5, H=4, bq=128, bk=64, sparsity=0.8, seed=33, name="22v q128/k64")
     assert 384 < L.n_kb <= 512
     _config_case(ress, L, 5, n_tokens=256, label="22v q128/k64")
@@ -318,40 +319,15 @@ def test_config_layer_stack(ress, layer):
     _config_case(ress, stack_layer(layer), 5, n_tokens=128, label=f"16v layer {layer}")
 
 
-def _launch_shape(H, n_qb, n_kb):
-    """Selection launch the library takes (the same rule, restated): slots per lane
-    by key-block count; then rows per workgroup among 8 (8 waves of 1 row), 4 (4
-    waves of 1), 16 (8 waves of 2) and 24 (8 waves of 3), by the fewest rounds of
-    workgroups over 256 compute units times (rows per wave + 1), 4 over 8 on a tie,
-    16 and 24 (only up to 384 key blocks) when strictly cheaper; 4 rows beyond 1088
-    key blocks."""
-    for lim, cpl, two in ((128, 2, True), (256, 4, True), (384, 6, True), (512, 8, False), (768, 12, False),
-                          (1088, 17, False), (2048, 32, None), (4096, 64, None)):
-        if n_kb <= lim:
-            break
-    if two is None:
-        return cpl, 4
-    cost = lambda rows, r: -(-(H * -(-n_qb // rows)) // 256) * (r + 1)
-    best, bc = 8, cost(8, 1)
-    if cost(4, 1) <= bc:
-        best, bc = 4, cost(4, 1)
-    if two:
-        if cost(16, 2) < bc:
-            best, bc = 16, cost(16, 2)
-        if cost(24, 3) < bc:
-            best, bc = 24, cost(24, 3)
-    return cpl, best
-
-
-# (key blocks of 64 tokens, heads, slots per lane, rows per workgroup): every launch
-# shape of the selection.
-LAUNCH_SHAPES = [(120, 35, 2, 24), (120, 18, 2, 16), (120, 9, 2, 8), (120, 1, 2, 4),
-                 (200, 21, 4, 24), (200, 11, 4, 16), (200, 6, 4, 8), (200, 1, 4, 4),
-                 (350, 12, 6, 24), (350, 6, 6, 16), (350, 3, 6, 8), (350, 1, 6, 4),
+# (key blocks of 64 tokens, heads, slots per lane, rows per workgroup). All shapes, at a milder
+# sparsity and with longer swap lists: test_gpu_select_shapes.
+LAUNCH_SHAPES = [(120, 35, 2, 24), (120, 18, 2, 12), (120, 9, 2, 8), (120, 1, 2, 4),
+                 (200, 21, 4, 24), (200, 11, 4, 12), (200, 6, 4, 8), (200, 1, 4, 4),
+                 (350, 12, 6, 24), (350, 6, 6, 12), (350, 3, 6, 8), (350, 1, 6, 4),
                  (450, 3, 8, 8), (450, 1, 8, 4),
                  (700, 2, 12, 8), (700, 1, 12, 4),
                  (1000, 2, 17, 8), (1000, 1, 17, 4),
-                 (1500, 1, 32, 4),
+                 (1500, 1, 24, 8),
                  (3000, 1, 64, 4)]
 
 
@@ -362,7 +338,7 @@ def test_select_launch_shapes(ress, n_kb, H, cpl, rows):
     cap."""
     L = synth.make_layer(8, n_kb * 8 - 5, 5, H=H, block=64, sparsity=0.75, seed=40 + cpl * 4 + rows,
                          name=f"{n_kb} blocks H={H}")
-    assert L.n_kb == n_kb and _launch_shape(L.H, L.n_qb, L.n_kb) == (cpl, rows)
+    assert L.n_kb == n_kb and select_shape(L.H, L.n_qb, L.n_kb) == (cpl, (12, 2) if rows == 24 else (rows, 1))
     say(f"[select launch shape] slots {cpl}, rows per workgroup {rows}: H={L.H} N={L.N} n_kb={L.n_kb}")
     rng = np.random.default_rng(cpl * 10 + rows)
     rows_s = np.unique(np.concatenate([rng.integers(0, L.H * L.n_qb, 120), [0, L.n_qb - 1, L.H * L.n_qb - 1]]))

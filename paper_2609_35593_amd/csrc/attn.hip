@@ -660,20 +660,31 @@ hipError_t launch_groups(const AttnParams &p, bool sparse, hipStream_t s)
     return hipGetLastError();
 }
 
-// Key groups per query block. One group where the rows fill the chip's 1,024 workgroup
-// places (four per CU at 128 queries) three times over; below that two, which halve
-// the time of a row and with it the last round and the rows that keep every block:
-// measured (us, one / two groups, 16 heads) 8 views 157 / 128 at 90% and 304 / 301 at
-// 50% sparsity, 16 views 434 / 309 at 90% and 540 / 543 at 75%, but 32 views 1,937 /
-// 2,071, where their shared barriers only cost. Four where even two leave most of the
-// chip idle (at most a workgroup per CU) and rows can be long enough to pay for the
-// merge: 4 heads of 4 views 69 / 54 / 47 with one / two / four.
+// Key groups per query block, by the layer's rows and its chunks per head (the most a
+// list can hold: the lists' own lengths are on the device). One rule for sparse and dense
+// attention, so that a list of every block gives the dense result bit for bit. Measured
+// with one against two groups, 128 queries unless 64 is said, us:
+//  - Two groups take 64 KB, two workgroups of them fill a CU: up to 512 rows, one round,
+//    they halve the time of a row (dense, 16 heads of 1,374 tokens 22 / 19.5; 64: 4 heads
+//    of 5,496 90 / 58), but for lists of a few chunks, where the merge costs more.
+//  - Up to 3,072 rows, three fillings of the 1,024 places of single groups, they shorten
+//    the last round and the rows that keep every block: 8 views 161 / 129 at 90% and
+//    294 / 279 at 50% sparsity, 16 views 380 / 313 at 90% and 564 / 548 at 75%; dense 8
+//    views 532 / 530, 16 views 1,948 / 1,973. That takes lists long enough: below 64 chunks
+//    (64 queries: 32) one group is faster (256 heads of 1,400 tokens, dense 148 / 173; 128
+//    heads of 2,000, 50% sparsity 109 / 128).
+//  - Above, their shared barriers only cost: 32 views 1,937 / 2,071.
+// Four where even two leave most of the chip idle (at most a workgroup per CU) and rows
+// can be long enough to pay for the merge: 4 heads of 4 views 69 / 54 / 47 with one / two
+// / four.
 template <int BQ, int BK>
 hipError_t launch_bk(const AttnParams &p, bool sparse, hipStream_t s)
 {
     const long long rows = (long long)p.H * p.n_qb;
-    if (rows <= 256 && p.n_kb * (BK / 64) >= 64) return launch_groups<BQ, BK, 4>(p, sparse, s);
-    if (rows <= 3072) return launch_groups<BQ, BK, 2>(p, sparse, s);
+    const int chunks = p.n_kb * (BK / 64);
+    if (rows <= 256 && chunks >= 64) return launch_groups<BQ, BK, 4>(p, sparse, s);
+    const int least = rows <= 512 ? 7 : BQ == 128 ? 64 : 32;
+    if (rows <= 3072 && chunks >= least) return launch_groups<BQ, BK, 2>(p, sparse, s);
     return launch_groups<BQ, BK, 1>(p, sparse, s);
 }
 

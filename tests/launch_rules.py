@@ -20,3 +20,12 @@ def select_shape(H, n_qb, n_kb):
     if cpl <= 2:
         options.append(((8, 2), rounds(16) // 2 * 215 + rounds(16) % 2 * 135))
     return cpl, min(options, key=lambda o: o[1])[0]  # the first of equals
+
+
+def attn_groups(H, n_qb, n_kb, bq, bk):
+    """Key groups per query block of the attention, by rows and by 64-key chunks per head."""
+    rows, chunks = H * n_qb, n_kb * (bk // 64)
+    if rows <= 256 and chunks >= 64:
+        return 4
+    least = 7 if rows <= 512 else 64 if bq == 128 else 32
+    return 2 if rows <= 3072 and chunks >= least else 1

@@ -5,13 +5,9 @@ test_gpu_attn_references.)"""
 import numpy as np
 import pytest
 
+from launch_rules import attn_groups
+
 pytestmark = pytest.mark.gpu
-
-
-def groups(H, n_qb, n_kb, bk):
-    """The library's rule, restated."""
-    rows = H * n_qb
-    return 4 if rows <= 256 and n_kb * (bk // 64) >= 64 else 2 if rows <= 3072 else 1
 
 
 def reference(q, k, v, count, idx, bq, bk, scale):
@@ -33,7 +29,10 @@ def reference(q, k, v, count, idx, bq, bk, scale):
 
 
 CASES = [(1, 70 * 64 - 5, 64, 64, 4), (2, 33 * 128 + 1, 128, 128, 4), (2, 40 * 128 - 64, 128, 128, 4), (3, 700, 64, 64, 2),
-         (3, 1100, 128, 128, 2), (2, 1025, 64, 128, 2), (2, 900, 128, 64, 2), (70, 45 * 64 + 3, 64, 64, 1)]
+         (3, 1100, 128, 128, 2), (2, 1025, 64, 128, 2), (2, 900, 128, 64, 2), (70, 45 * 64 + 3, 64, 64, 1),
+         # both sides of the rule's lines: 7 chunks, 512 rows with 31 and 32, 63 and 64 chunks
+         (1, 6 * 64, 64, 64, 1), (1, 7 * 64 - 9, 64, 64, 2), (18, 31 * 64 - 7, 64, 64, 1), (18, 32 * 64 - 7, 64, 64, 2),
+         (17, 63 * 64, 128, 64, 1), (17, 64 * 64 - 1, 128, 128, 2)]
 
 
 @pytest.mark.parametrize("spread", [1.0, 30.0])
@@ -44,7 +43,7 @@ def test_groups(H, N, bq, bk, G, spread):
     import paper_2609_35593_amd as ress
 
     n_qb, n_kb = -(-N // bq), -(-N // bk)
-    assert groups(H, n_qb, n_kb, bk) == G
+    assert attn_groups(H, n_qb, n_kb, bq, bk) == G
     rng = np.random.default_rng(H * 1000 + N)
     gen = torch.Generator().manual_seed(N + int(spread))
     q, k, v = (torch.randn(H, N, 64, generator=gen) for _ in range(3))
@@ -85,7 +84,7 @@ def test_groups(H, N, bq, bk, G, spread):
     assert float(err.max()) <= bound and float(err.mean()) <= 2e-3, (float(err.max()), bound, float(err.mean()))
 
 
-@pytest.mark.parametrize("N,G", [(256, 2), (4096, 4)])
+@pytest.mark.parametrize("N,G", [(512, 2), (4096, 4)])
 def test_groups_share_one_form_of_the_scores(N, G):
     """A row's first 64 keys choose between pre-scaled and exact scores for all of its groups: the other chunks' logits
     are large, equal in two chunks of different groups and opposite in V, so the output is the difference of the two
@@ -94,7 +93,7 @@ def test_groups_share_one_form_of_the_scores(N, G):
 
     import paper_2609_35593_amd as ress
 
-    assert groups(1, N // 128, N // 64, 64) == G
+    assert attn_groups(1, N // 128, N // 64, 128, 64) == G
     q, k, v = (torch.zeros(1, N, 64) for _ in range(3))
     q[0, :, 0] = torch.linspace(50.0, 60.0, N)  # base-2 logits of 90 to 108 against 10, about 1 against 0.1
     k[0, :, 0] = 0.1

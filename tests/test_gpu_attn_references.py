@@ -7,6 +7,8 @@ these before anything is compared."""
 import numpy as np
 import pytest
 
+from launch_rules import attn_groups
+
 pytestmark = pytest.mark.gpu
 
 SCALE_LOG2 = np.float32(0.125) * np.float32(1.4426950408889634)
@@ -94,10 +96,9 @@ def test_references(H, N, bq, bk, G):
     import torch
 
     import paper_2609_35593_amd as ress
-    from test_gpu_attn_groups import groups
 
     n_qb, n_kb = -(-N // bq), -(-N // bk)
-    assert groups(H, n_qb, n_kb, bk) == G
+    assert attn_groups(H, n_qb, n_kb, bq, bk) == G
     q, k, v, prof = layer(N)
     L, inside = logits(q, k)
     check_profiles(L, inside, prof, G)

@@ -2,24 +2,23 @@
 // all key blocks (dense), bf16 inputs, bf16 MFMA products with float32
 // accumulation, float32 online softmax.
 //
-// One workgroup per (head, query block), BQ/32 waves, each wave owning 32 query
-// rows. The score tile is computed transposed, S^T = K Q^T, with
-// v_mfma_f32_32x32x16_bf16: its accumulator puts one query per lane (lane l and
-// l+32 share query l%32, each holding 16 of every 32 keys), so row sums stay in
-// the lane except for one exchange with lane l^32, and the probabilities already
-// sit in the B-operand layout of O^T = V^T P^T.
+// One workgroup per (head, query block), G groups of BQ/32 waves (G = 1 but for small
+// layers, see launch_bk), each wave owning 32 query rows. The score tile is computed
+// transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16: its accumulator puts one
+// query per lane (lane l and l+32 share query l%32, each holding 16 of every 32 keys),
+// so row sums stay in the lane except for one exchange with lane l^32, and the
+// probabilities already sit in the B-operand layout of O^T = V^T P^T.
 //
-// Keys are consumed in 64-key chunks (one 64-key block of the kept list, or half
-// of a 128-key block). A chunk is two 32-key sub-tiles; a wave issues
-// the 4 score MFMAs of each, forms the probabilities and issues the 8 PV MFMAs. Latency is
-// hidden by occupancy rather than by a software pipeline across chunks:
-// K and V chunks sit in two-slot rings of 8 KB per tensor and slot (32 KB per
-// workgroup), and the kernel fits 128 registers, so four 128-query workgroups
-// share a CU (four waves per SIMD), and the matrix and vector pipes of a SIMD
-// serve whichever of its waves is ready. (Measured: at D = 64 the softmax needs
-// about as many issue slots as the MFMAs; two waves per SIMD with a software
-// pipeline reached the same rate as three without one, four waves run 4-8%
-// faster.)
+// Keys are consumed in 64-key chunks (one 64-key block of the kept list, or half of a
+// 128-key block). A chunk is two 32-key sub-tiles; a wave issues the 4 score MFMAs of
+// each, forms the probabilities and issues the 8 PV MFMAs. Latency is hidden by
+// occupancy rather than by a software pipeline across chunks: K and V chunks sit in
+// two-slot rings of 8 KB per tensor and slot (32 KB per group), and the kernel fits
+// 128 registers, so four single-group 128-query workgroups, or two of two groups or
+// one of four, share a CU (four waves per SIMD), and the matrix and vector pipes of a
+// SIMD serve whichever of its waves is ready. (Measured: at D = 64 the softmax needs
+// about as many issue slots as the MFMAs; two waves per SIMD with a software pipeline
+// reached the same rate as three without one, four waves run 4-8% faster.)
 //
 // Chunks move from global memory straight into LDS (buffer_load ... lds, 16
 // bytes per lane, 1 KB per wave instruction, 32-bit offsets against a per-head
@@ -514,7 +513,8 @@ __global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(con
             if (!zref) {
                 load_q(false);
                 cw = c;
-                if (fabsf(m0) < INFINITY) mref = m0 + kHeadroom;
+                // (A whole number: the probabilities round as they do against reference 0.)
+                if (fabsf(m0) < INFINITY) mref = rintf(m0) + kHeadroom;
                 wait_vm_all();  // Q lands here, not at the first MFMA of every chunk
             }
         }
@@ -525,8 +525,8 @@ __global__ void __launch_bounds__(BQ * 2 * G, BQ == 128 ? 4 : 2) attn_kernel(con
         // then); its Q stays pre-scaled (cw = 1), so every score of a row has one form.
         bool fetched = false;
         if (zref) {
-            auto zero_chunk = [&](const unsigned char *ks, const unsigned char *vs, unsigned char *kd, unsigned char *vd)
-                                  __attribute__((always_inline)) -> bool {
+            auto zero_chunk = [&](const unsigned char *ks, const unsigned char *vs, unsigned char *kd,
+                                  unsigned char *vd) __attribute__((always_inline)) -> bool {
                 bf16x8 p0[2], p1[2];
                 float lh;
                 fetch(ch, kd, vd);

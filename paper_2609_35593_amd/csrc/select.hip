@@ -378,7 +378,8 @@ __global__ void __launch_bounds__(NW * 64, NW * WPC / 4) select_kernel(const Sel
     // Keeps the compiler from interleaving the work of more than FENCE slots, whose
     // temporaries would not fit the registers.
     auto slot_fence = [&](int c) __attribute__((always_inline)) {
-        if (Cfg::FENCE > 0 && c % (Cfg::FENCE > 0 ? Cfg::FENCE : 1) == Cfg::FENCE - 1) __builtin_amdgcn_sched_barrier(0);
+        if (Cfg::FENCE > 0 && c % (Cfg::FENCE > 0 ? Cfg::FENCE : 1) == Cfg::FENCE - 1)
+            __builtin_amdgcn_sched_barrier(0);
     };
     // n_kb anew for each use, so that the compiler compares a slot's block index with it
     // there instead of keeping one mask per slot.

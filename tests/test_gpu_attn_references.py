@@ -121,3 +121,30 @@ def test_references(H, N, bq, bk, G):
     bound = (2.0 ** -8 + 2.0 ** -13) * 1.01 * spread + 2.0 ** -16 * (w @ v.double().abs())
     over = ((got - ref).abs() / bound).max(1).values
     assert float(over.max()) <= 1.0, [(int(p), float(over[prof == p].max())) for p in prof.unique()]
+
+
+@pytest.mark.parametrize("H,N,bq,bk", [(1, 700, 64, 64), (1, 4500, 128, 128), (256, 850, 64, 128)])
+def test_first_references_round_like_zero(H, N, bq, bk):
+    """Waves that start outside the band with logits of up to 49: their references are whole numbers, so the
+    probabilities round to bf16 as 2^logit does, and the output is that of the weights so rounded (an eighth of the
+    rounding's own effect is left for exponentials that land on the other side of a rounding boundary)."""
+    import torch
+
+    import paper_2609_35593_amd as ress
+
+    gen = torch.Generator().manual_seed(N)
+    q, k, v = (torch.randn(N, 64, generator=gen) for _ in range(3))
+    q, k, v = (5.5 * q).bfloat16(), k.bfloat16(), v.bfloat16()
+    q[::32] = (30.0 / float(SCALE_LOG2) / k[0].float().square().sum() * k[:1].float()).bfloat16()  # 30 in every wave
+    L, inside = logits(q, k)
+    assert not bool(inside.any()) and float(L.max()) < 49.0
+    dev = [x.cuda().expand(H, N, 64).contiguous() for x in (q, k, v)]
+    n_qb, n_kb = -(-N // bq), -(-N // bk)
+    count = torch.full((H, n_qb), n_kb, dtype=torch.int32, device="cuda")
+    idx = torch.arange(n_kb, dtype=torch.int32, device="cuda").expand(H, n_qb, n_kb).contiguous()
+    got = ress.ress_sparse_attn_out_f32(*dev, count, idx, bq=bq, bk=bk)[0].cpu().double()
+    w = torch.exp2(L)
+    ref = (w / w.sum(1, keepdim=True)) @ v.double()
+    w = w.float().bfloat16().double()
+    rounded = (w / w.sum(1, keepdim=True)) @ v.double()
+    assert float((got - rounded).norm()) <= 0.125 * float((rounded - ref).norm())

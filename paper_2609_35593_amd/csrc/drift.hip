@@ -21,7 +21,7 @@
 //    wave and stay in registers.
 // Roofline: 0.90 GFLOP of float64 matrix steps (40 a tile) and 90 MB (two float32 inputs)
 // at 16 heads x 10,992 tokens, 11.5 and 18 us at 78.6 TFLOP/s and 5.1 TB/s. Measured there:
-// 30 us (one lane per channel with M and x read from LDS for every token: 145 us).
+// 28 us (one lane per channel with M and x read from LDS for every token: 145 us).
 #include "ress_internal.h"
 
 namespace ress {

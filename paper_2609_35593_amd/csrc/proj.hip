@@ -21,11 +21,12 @@
 // take 9 (QKV) to 16 us (residual, one dependent load after another): one workgroup
 // fits a CU, so nothing hides it. Residual pieces are now loaded a phase ahead, and
 // stores go out in batches of eight. Measured (us, before -> now, back to back): QKV
-// projection 98 -> 87 at 8 views, 170 -> 156 at 16, 322 -> 292 at 32 (277 GFLOP, 950
-// TFLOP/s); output projection, bf16 stream 117 -> 104 at 32 views, 69 -> 56 at 16,
-// 32 -> 18 at 2. (Two workgroups of 128 x 256 tiles per CU, each hiding the other's
-// epilogue, reached 169 and 125 us at 16 and 32 views: they fetch 1.5 times the
-// operand bytes past L2, which the k-loop then waits for.)
+// projection 98 -> 87 at 8 views, 170 -> 156 at 16, 316 -> 290 at 32 (277 GFLOP, 950
+// TFLOP/s; with the caches flushed before each call 348 -> 315, between other kernels and
+// with cold operands, as bench.py times it, 370 -> 339); output projection, bf16 stream
+// 117 -> 104 at 32 views, 69 -> 56 at 16, 32 -> 18 at 2. (Two workgroups of 128 x 256
+// tiles per CU, each hiding the other's epilogue, reached 169 and 125 us at 16 and 32
+// views: they fetch 1.5 times the operand bytes past L2, which the k-loop then waits for.)
 #include "ress_internal.h"
 
 namespace ress {

@@ -243,15 +243,15 @@ __device__ __forceinline__ unsigned int search_high(const unsigned int (&h)[NS],
 
 // Exact top-k of the member slots by (key desc, block index asc). The slots' order
 // keys are the 8-byte words keys[64 c] (this lane's pointer into its wave's LDS row;
-// they are read from there for each search, which needs one register a slot). Bit c of mbits marks
-// this lane's slot c as a member. Non-member high words are replaced by 0, below
-// every member's (an order key of a finite value has a nonzero high word), so one
-// ballot per slot counts members only. search_high first; where no high word
-// separates the top k, a key reaches a candidate (t, x) (x >= 1), t the k-th largest
-// high word, exactly when the 32-bit value "all ones if its high word is above t, its
-// low word if equal, zero if below" reaches x, and the low word is found bit by bit.
-// Returns this lane's chosen slots as a bit mask. Requires 0 <= k <= number of
-// members.
+// they are read from there for each search, which needs one register a slot). Bit c
+// of mbits marks this lane's slot c as a member. Non-member high words are replaced
+// by 0, below every member's (an order key of a finite value has a nonzero high
+// word), so one ballot per slot counts members only. search_high first; where no
+// high word separates the top k, a key reaches a candidate (t, x) (x >= 1), t the
+// k-th largest high word, exactly when the 32-bit value "all ones if its high word
+// is above t, its low word if equal, zero if below" reaches x, and the low word is
+// found bit by bit. Returns this lane's chosen slots as a bit mask. Requires 0 <= k
+// <= number of members.
 template <int CPL>
 __device__ __forceinline__ typename slot_bits<(CPL > 32)>::type topk_slots(const double *keys,
                                                                            typename slot_bits<(CPL > 32)>::type mbits,
@@ -884,9 +884,9 @@ __global__ void __launch_bounds__(NW * 64, NW * WPC / 4) select_kernel(const Sel
             double mr = 0.0, md = 0.0;
             // The swapped blocks, in slot order, are gathered into a list of (block, weight)
             // pairs in the row's staging row (its keys are no longer needed; where the row
-            // might not hold them all, half of the slots at a time) and applied 8 rows of
-            // Vbar at a time: restores subtract d_k, drops add it. The list is padded to a multiple of 8 with
-            // zero-weight entries of block 0, which leave g unchanged.
+            // might not hold them all, half of the slots at a time) and applied 8 rows of Vbar
+            // at a time: restores subtract d_k, drops add it. The list is padded to a multiple
+            // of 8 with zero-weight entries of block 0, which leave g unchanged.
             int lane_here = lane;  // block indices formed here, not kept per slot
             asm("" : "+v"(lane_here));
             constexpr int HALF = (CPL + 1) / 2;
